@@ -232,3 +232,93 @@ def test_refit_improves_chi2_and_recovers_momentum(gpu_available):
     assert len(ratios) > 100
     assert abs(np.median(ratios) - 1.0) < 0.01
     assert np.quantile(np.abs(ratios - 1.0), 0.68) < 0.05
+
+
+def _sized(sizes, seed=77):
+    """Candidates of exactly these hit counts: hits of one exact helix each,
+    sampled along one turn (any number of them), with 0.05 mm of noise."""
+    rng = np.random.default_rng(seed)
+    r, z, v = [], [], []
+    for n in sizes:
+        R, d0, phi0 = rng.uniform(120, 260), rng.uniform(60, 120), rng.uniform(0, 2 * math.pi)
+        cx, cy = (R + d0) * math.sin(phi0), -(R + d0) * math.cos(phi0)
+        vane = rng.integers(0, eventgen.N_VANES, n)
+        ang = 2 * math.pi * vane / eventgen.N_VANES
+        b = np.cos(ang) * cx + np.sin(ang) * cy
+        sq = np.sqrt(np.maximum(b * b - d0 * (d0 + 2 * R), 0.0))
+        t = b + np.where(rng.random(n) < 0.5, 1.0, -1.0) * sq
+        r.append((np.abs(t) + rng.normal(0, 0.05, n)).astype(np.float32))
+        z.append(rng.uniform(-150, 150, n).astype(np.float32))
+        v.append(vane.astype(np.int16))
+    return r, z, v
+
+
+def _refit_all(per, n_vanes=eventgen.N_VANES):
+    """Bytes of everything the refit calls write, per candidate."""
+    import torch
+    from paper_2511_02742_amd.hough import RefitHits, refit_chi2, refit_gauss_newton, refit_grad, refit_init
+    dev = torch.device("cuda", 0)
+    n = np.array([len(p[0]) for p in per], np.int64)
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    cat = [np.concatenate([p[k] for p in per]) for k in range(3)]
+    t = [torch.from_numpy(x).to(dev) for x in cat]
+    h = RefitHits(torch.from_numpy(off).to(dev), t[0], t[1], t[2], n_vanes)
+    p0 = refit_init(h).contiguous()
+    p = (p0 + torch.tensor([0.0, 2e-3, 0.3, 0.4, 5e-3], device=dev)).contiguous()
+    chi2, grad = refit_chi2(h, p), refit_grad(h, p)
+    pn = p0.clone()
+    fit = refit_gauss_newton(h, pn)
+    host = {k: x.cpu().numpy() for k, x in dict(p0=p0, p=p, chi2=chi2, grad=grad, pn=pn, fit=fit, status=h.status).items()}
+    sign, aref = h.sign.cpu().numpy(), h.aref.cpu().numpy()
+    rows = []
+    for c in range(len(per)):
+        sl = slice(off[c], off[c + 1])
+        rows.append({**{k: x[c] for k, x in host.items()}, "sign": sign[sl], "aref": aref[sl]})
+    return rows
+
+
+@pytest.mark.parametrize("sizes", [
+    (1, 2, 3, 4, 6, 63, 64, 65, 128, 129, 0, 12, 200, 7, 300, 5, 13),      # refused ones among them; a wave's hits past one, two and more rounds
+    (20,) * 8 + (32,) * 8 + (33,) * 8,                                     # hits of one wave at and around one and two rounds
+    (9,),
+])
+def test_refit_does_not_depend_on_the_wave_a_candidate_shares(gpu_available, sizes):
+    # the sums over a candidate's hits run in hit order whatever candidates
+    # are taken together, so each alone gives the same bytes
+    per = list(zip(*_sized(sizes)))
+    together = _refit_all(per)
+    alone = [_refit_all([p])[0] for p in per if len(p[0]) > 0]
+    at = 0
+    for c, p in enumerate(per):
+        if len(p[0]) == 0:
+            continue
+        for k, x in alone[at].items():
+            assert np.asarray(x).tobytes() == np.asarray(together[c][k]).tobytes(), (c, len(p[0]), k)
+        at += 1
+        n, row = len(p[0]), together[c]
+        assert row["status"] == (1 if n < 3 else 2 if n > 128 else row["status"]) and row["status"] in (0, 1, 2, 3)
+        if row["status"] != 0:
+            assert np.all(row["p0"] == 0) and np.all(row["sign"] == 1) and np.all(row["aref"] == 0)
+            continue
+        p0, s0, a0 = o_init(*p)
+        assert np.array_equal(row["sign"], s0.astype(np.float32))
+        assert np.allclose(row["aref"], a0, atol=2e-6 * max(1.0, np.abs(a0).max()))
+        assert np.all(_rel(row["p0"].astype(np.float64), p0) < 2e-6)
+        # float32 residuals to about 1e-4 sigma (the bound of the pileup candidates above)
+        wc = o_chi2(row["p"].astype(np.float64), *p, row["sign"], row["aref"])
+        assert abs(row["chi2"] - wc) <= 1e-3 * max(wc, 1.0)
+
+
+def test_refit_order_of_equal_and_missing_z(gpu_available):
+    # equal z keep hit order; a NaN z leaves the circle's parameters as they are
+    r, z, v = _sized((12, 12, 12))
+    z[0][:6] = z[0][0]
+    z[1][:] = np.float32(7.0)                       # flat: the largest angular gap
+    rows = _refit_all(list(zip(r, z, v)))
+    for c in (0, 1):
+        p0, s0, a0 = o_init(r[c], z[c], v[c])
+        assert rows[c]["status"] == 0 and np.allclose(rows[c]["aref"], a0, atol=2e-5)
+    z[2][4] = np.nan
+    nan = _refit_all(list(zip(r, z, v)))
+    assert np.array_equal(nan[2]["p0"][:3], rows[2]["p0"][:3]) and np.isnan(nan[2]["p0"][3:]).all()
+    assert nan[0]["pn"].tobytes() == rows[0]["pn"].tobytes()
