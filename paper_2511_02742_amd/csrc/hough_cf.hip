@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include "hough_internal.h"
+#include "hough_tw.h"
 #include "hough_wave.h"
 
 namespace hough {
@@ -330,10 +331,12 @@ __device__ void write_error_counts(int64_t *counts, long long status, long long 
     for (int i = HOUGH_COUNT_EVALS; i < HOUGH_COUNTS; ++i) counts[i] = 0;
 }
 
+// The whole loop of event e, whose n64 hits start at b, by the workgroup (b and
+// n64 uniform).
 template <int NT>
-__global__ __launch_bounds__(NT) void k_find_cf(FindArgs A, const float2 *__restrict__ ccs,
-                                                const float2 *__restrict__ cs) {
-    __shared__ CfShared sh;
+__device__ __forceinline__ void find_cf_event(const FindArgs &A, const float2 *__restrict__ ccs,
+                                              const float2 *__restrict__ cs, CfShared &sh, int e, int64_t b,
+                                              int64_t n64) {
     unsigned char *const lds = reinterpret_cast<unsigned char *>(cf_lds);
     const int cb = (4 * A.c_theta * A.c_rho + 15) & ~15;
     const int fb = (4 * A.f_theta * A.f_rho + 15) & ~15;
@@ -345,9 +348,6 @@ __global__ __launch_bounds__(NT) void k_find_cf(FindArgs A, const float2 *__rest
     L.mm = L.pool + kSegWords;
     L.red = L.mm + kSegWords;
 
-    const int e = A.order != nullptr ? __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]) : (int)blockIdx.x;
-    const int64_t b = uniform64(A.offsets[e]);
-    const int64_t n64 = uniform64(A.offsets[e + 1]) - b;
     if (threadIdx.x == 0) {
         if (A.ev_clock != nullptr) sh.t_start = wall_clock64();
         int bad = 0;
@@ -462,6 +462,30 @@ __global__ __launch_bounds__(NT) void k_find_cf(FindArgs A, const float2 *__rest
     }
 }
 
+template <int NT>
+__global__ __launch_bounds__(NT) void k_find_cf(FindArgs A, const float2 *__restrict__ ccs,
+                                                const float2 *__restrict__ cs) {
+    __shared__ CfShared sh;
+    const int e = A.order != nullptr ? __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]) : (int)blockIdx.x;
+    const int64_t b = uniform64(A.offsets[e]);
+    find_cf_event<NT>(A, ccs, cs, sh, e, b, uniform64(A.offsets[e + 1]) - b);
+}
+
+// The window loop of the time-sliced finder (hough_tw.h) with this finder.
+template <int NT>
+__device__ __noinline__ void find_cf_event_call(const FindArgs *A, int e, int64_t b, int64_t n) {
+    __shared__ CfShared sh;
+    const FindArgs &a = tw::const_args(A);
+    find_cf_event<NT>(a, a.ccs, a.cs, sh, __builtin_amdgcn_readfirstlane(e), uniform64(b), uniform64(n));
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void k_tw_run_cf(TwArgs W) {
+    __shared__ tw::Shared T;
+    tw::run<NT>(W, tw::const_args(W.find), cf_lds, T,
+                [&](int e, int64_t b, int64_t n) { find_cf_event_call<NT>(W.find, e, b, n); });
+}
+
 }  // namespace
 
 int cf_lds_bytes(int c_bins, int f_bins, int wg_threads) {
@@ -497,6 +521,31 @@ hipError_t set_cf_lds_limit(int wg_threads, int lds_bytes) {
     default:
         return hipErrorInvalidValue;
     }
+}
+
+hipError_t set_tw_cf_lds_limit(int wg_threads, int lds_bytes) {
+    const void *f = wg_threads == 256   ? reinterpret_cast<const void *>(k_tw_run_cf<256>)
+                    : wg_threads == 512 ? reinterpret_cast<const void *>(k_tw_run_cf<512>)
+                                        : reinterpret_cast<const void *>(k_tw_run_cf<1024>);
+    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+}
+
+hipError_t launch_tw_run_cf(const TwArgs &t, int wg_threads, int lds_bytes, hipStream_t s) {
+    const dim3 grid(t.n_tl);
+    switch (wg_threads) {
+    case 256:
+        hipLaunchKernelGGL(k_tw_run_cf<256>, grid, dim3(256), lds_bytes, s, t);
+        break;
+    case 512:
+        hipLaunchKernelGGL(k_tw_run_cf<512>, grid, dim3(512), lds_bytes, s, t);
+        break;
+    case 1024:
+        hipLaunchKernelGGL(k_tw_run_cf<1024>, grid, dim3(1024), lds_bytes, s, t);
+        break;
+    default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_find_cf(const FindArgs &a, int wg_threads, int lds_bytes, hipStream_t s) {

@@ -16,6 +16,7 @@
 #include "hough_internal.h"
 #include "hough_runtime.h"
 #include "hough_tf.h"
+#include "hough_tw.h"
 
 // Scratch of the allocation-free finder entry point (hough_find_noalloc):
 // the finder workspace for one call at a time per device, laid out afresh
@@ -74,6 +75,7 @@ constexpr int kSingleSweepGroups = 32;
 constexpr int kSingleSweepThreads = 256;
 constexpr int kSmallCall = 8;
 constexpr int kBandCall = 64;             // calls of up to this many events may run k_band
+constexpr int kTwCfLds = 48 << 10;        // LDS the time-sliced finder takes at least in mode 2 (windows of about 2000 hits)
 constexpr int64_t kRegisterHits = 512;    // alive hits the finder holds in registers
 // k_band also takes events of fewer hits than the register batch, from this
 // many on: about where a pileup event's window-test peaks outgrow the
@@ -299,6 +301,13 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         if (c.band_lds + kStaticLds <= lds_max && hough::set_band_lds_limit(c.band_lds) == hipSuccess)
             c.band_split = 1;
     }
+    // the time-sliced finder stages a window's hits in the finder's LDS
+    // between its calls
+    c.tw_lds = c.lds_bytes;
+    if (g.peak_mode != 2 && hough::set_tw_lds_limit(c.wg_threads, c.tw_lds) != hipSuccess) {
+        why = "hipFuncSetAttribute failed for the time-sliced finder";
+        return HOUGH_ERR_DEVICE;
+    }
     int drows = std::min(g.n_theta, std::max(1, (lds_max - kStaticLds) / row_bytes));
     c.dump_rows = std::min(drows, 64);
     c.dump_lds = c.dump_rows * row_bytes;
@@ -325,6 +334,11 @@ hough_status choose_shape(Ctx &c, std::string &why) {
             return HOUGH_ERR_DEVICE;
         }
         c.max_resident = per_cu * prop.multiProcessorCount;
+        c.tw_lds = std::max(c.lds_bytes, kTwCfLds);
+        if (hough::set_tw_cf_lds_limit(c.wg_threads, c.tw_lds) != hipSuccess) {
+            why = "hipFuncSetAttribute failed for the time-sliced finder";
+            return HOUGH_ERR_DEVICE;
+        }
     }
     return HOUGH_OK;
 }
@@ -483,20 +497,19 @@ hough::FindArgs find_args(const Ctx &c, const Workspace &w) {
 hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events, int64_t n_total,
                           const int64_t *offsets, const float *z, const int16_t *vane, int32_t max_iters,
                           hough_candidate *cand, int32_t *hit_index, int64_t *counts, bool timed,
-                          bool longest_first, bool total_is_bound, bool ws_only) {
+                          bool longest_first) {
     hough::FindArgs a = find_args(c, w);
     a.n_events = n_events;
     a.n_total = n_total;
-    a.total_is_bound = total_is_bound ? 1 : 0;
     a.offsets = offsets;
     a.z = z;
     a.vane = vane;
     a.max_iters = max_iters;
-    const bool single = n_events == 1 && !ws_only;
+    const bool single = n_events == 1;
     // k_band: a call of a few tens of events sweeps its large events' first
     // band ahead of the finder, over one workgroup per finder wave each
     const bool band = n_events > 0 && n_events <= kBandCall && c.band_split && c.sweep_groups == 0 &&
-                      !total_is_bound && w.pool_slots >= n_events && n_total > kBandMinHits;
+                      w.pool_slots >= n_events && n_total > kBandMinHits;
     a.band_min = band ? (int32_t)kBandMinHits : (int32_t)kRegisterHits;
     if (single) {
         a.counts = counts;
@@ -507,7 +520,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
         // a few events: each one's first sweep spread over several workgroups
         // (the sweep kernel takes events of up to band_min hits; a lone
         // larger event skips it)
-        if (!(n_events == 1 && n_total > a.band_min && !total_is_bound)) {
+        if (!(n_events == 1 && n_total > a.band_min)) {
             a.g_hs = w.g_hs;
             hipError_t ss = hough::launch_sweep(a, kSingleSweepThreads, kSingleSweepGroups, s);
             if (ss != hipSuccess)
@@ -549,7 +562,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
         (void)hipEventRecord(e1, s);
         c.ev_pairs.emplace_back(e0, e1);
     }
-    if (single || ws_only) return HOUGH_OK;
+    if (single) return HOUGH_OK;
     hough::CompactArgs ca{};
     ca.n_events = n_events;
     ca.n_total = n_total;

@@ -31,6 +31,7 @@
 #include <hip/hip_runtime.h>
 
 #include "hough_internal.h"
+#include "hough_tw.h"
 #include "hough_wave.h"
 
 #include <algorithm>
@@ -372,7 +373,7 @@ struct Shared {
     // 512 hits; larger events keep theirs in device memory
     uint16_t aidx_s[kChunks * kWave];
 };
-static_assert(sizeof(Shared) <= kStaticLds, "the host leaves kStaticLds bytes of LDS for the finder's static state");
+static_assert(sizeof(Shared) + sizeof(tw::Shared) <= kStaticLds, "the host leaves kStaticLds bytes of LDS for the finder's static state");
 
 // Charges the cycles since the last mark to phase k (thread 0; the marks sit
 // after a workgroup barrier, so thread 0's counter stands for the group).
@@ -2304,9 +2305,6 @@ __device__ void put_ev_stats(const FindArgs &A, int e, unsigned long long evals,
     p[kEvVotes * ne] = votes;
 }
 
-// At most 128 VGPRs at every width (four waves per SIMD): a 512-thread
-// finder whose tile leaves half the LDS free then shares a CU with another
-// event's workgroup, and a 256-thread one with up to three.
 // The event's clock stamps; in the HOUGH_PHASE_CLOCKS build, instead, its
 // cycles per phase (ev_clock[16 e + k], phase k; rest of the event's cycles
 // included in kPhRest).
@@ -2322,12 +2320,9 @@ __device__ __forceinline__ void put_phases(const FindArgs &A, int e, Shared &sh)
 #endif
 }
 
-template <int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_find(FindArgs A,
-                                                                                   const float2 *__restrict__ cs) {
-    constexpr int NW = NT / kWave;
+// The finder's dynamic LDS (see Lds).
+__device__ __forceinline__ Lds find_lds(const FindArgs &A) {
     unsigned char *const lds = reinterpret_cast<unsigned char *>(g_lds);
-    __shared__ Shared sh;
     Lds L;
     L.tile = reinterpret_cast<uint32_t *>(lds);
     L.hot = reinterpret_cast<uint32_t *>(lds + A.tile_bytes);
@@ -2336,15 +2331,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     L.dummy = reinterpret_cast<uint32_t *>(L.pbuf + (A.pkeep + A.hcap));
     L.hs = reinterpret_cast<unsigned long long *>(lds + A.hs_off);
     L.sorted = reinterpret_cast<unsigned long long *>(lds + A.sorted_off);
+    return L;
+}
 
-    const int e = A.order != nullptr ? __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]) : (int)blockIdx.x;
+// The whole find-and-remove loop of event e, whose n64 hits start at b, by the
+// workgroup (b and n64 uniform, in scalar registers).
+template <int NT>
+__device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__restrict__ cs, const Lds &L, Shared &sh,
+                                           int e, int64_t b, int64_t n64) {
+    constexpr int NW = NT / kWave;
     const int wave = wave_id();
     const int lane = lane_id();
-    // the event's bounds are uniform: keep them (and every address derived
-    // from them) in scalar registers
-    const int64_t b = uniform64(A.offsets[e]);
-    const int64_t n64 = uniform64(A.offsets[e + 1]) - b;
-
     if (tid_x() == 0) {
         if (A.ev_clock != nullptr) sh.t_start = wall_clock64();
 #ifdef HOUGH_PHASE_CLOCKS
@@ -2759,6 +2756,42 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         put_ev_stats(A, e, evals, iter, passes, tiled, sh.n_trunc, sh.n_hotscan, hs_full, recounts, bigs, votes);
         put_phases(A, e, sh);
     }
+}
+
+// At most 128 VGPRs at every width (four waves per SIMD): a 512-thread
+// finder whose tile leaves half the LDS free then shares a CU with another
+// event's workgroup, and a 256-thread one with up to three.
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_find(FindArgs A,
+                                                                                   const float2 *__restrict__ cs) {
+    __shared__ Shared sh;
+    const int e = A.order != nullptr ? __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]) : (int)blockIdx.x;
+    // the event's bounds are uniform: keep them (and every address derived
+    // from them) in scalar registers
+    const int64_t b = uniform64(A.offsets[e]);
+    find_event<NT>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
+}
+
+// The event finder as a call: inlined into the window loop below, the values
+// that the compiler keeps over the loop took 1136 B of scratch a lane; the call
+// saves and restores 20 registers instead. *A is read with scalar loads, like a
+// kernel's arguments (vector loads held in registers: 480 B).
+template <int NT>
+__device__ __noinline__ void find_event_call(const FindArgs *A, int e, int64_t b, int64_t n) {
+    __shared__ Shared sh;
+    const FindArgs &a = tw::const_args(A);
+    find_event<NT>(a, a.cs, find_lds(a), sh, __builtin_amdgcn_readfirstlane(e), uniform64(b), uniform64(n));
+}
+
+// The window loop of the time-sliced finder: one workgroup per timeline, which
+// runs find_event on each window that needs it (see hough_tw.h). Workgroups of
+// the finder's own shape, so no more are resident at once than it has
+// large-event slots.
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_tw_run(TwArgs W) {
+    __shared__ tw::Shared T;
+    tw::run<NT>(W, tw::const_args(W.find), g_lds, T,
+                [&](int e, int64_t b, int64_t n) { find_event_call<NT>(W.find, e, b, n); });
 }
 
 // First histogram sweep of each event split over `groups` workgroups: group g
@@ -3284,6 +3317,31 @@ hipError_t set_find_lds_limit(int wg_threads, int lds_bytes) {
     default:
         return hipErrorInvalidValue;
     }
+}
+
+hipError_t set_tw_lds_limit(int wg_threads, int lds_bytes) {
+    const void *f = wg_threads == 256   ? reinterpret_cast<const void *>(k_tw_run<256>)
+                    : wg_threads == 512 ? reinterpret_cast<const void *>(k_tw_run<512>)
+                                        : reinterpret_cast<const void *>(k_tw_run<1024>);
+    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+}
+
+hipError_t launch_tw_run(const TwArgs &t, int wg_threads, int lds_bytes, hipStream_t s) {
+    const dim3 grid(t.n_tl);
+    switch (wg_threads) {
+    case 256:
+        hipLaunchKernelGGL(k_tw_run<256>, grid, dim3(256), lds_bytes, s, t);
+        break;
+    case 512:
+        hipLaunchKernelGGL(k_tw_run<512>, grid, dim3(512), lds_bytes, s, t);
+        break;
+    case 1024:
+        hipLaunchKernelGGL(k_tw_run<1024>, grid, dim3(1024), lds_bytes, s, t);
+        break;
+    default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 hipError_t set_dump_lds_limit(int lds_bytes) {

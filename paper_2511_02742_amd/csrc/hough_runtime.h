@@ -71,6 +71,7 @@ struct Ctx {
     int big_sort = 0;                         // longest equal-count run sorted in LDS
     int big_ok = 0, roll_off = 0, roll_bytes = 0;  // banded large-event sweep
     int max_resident = 0;                     // finder workgroups resident at once on the device
+    int tw_lds = 0;                           // LDS of the time-sliced finder's workgroups
     double safe_r2 = -1.0;
     int dump_rows = 0, dump_lds = 0;
     Workspace ws;
@@ -117,17 +118,14 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
 void free_workspace(Workspace &w);
 // Enqueues one finder call on s (split sweep, finder, compaction); outputs
 // as in hough_find. With longest_first, a call of many events runs its
-// longest events first (an ordering kernel ahead of the finder). With
-// total_is_bound, n_total only bounds offsets[n_events] (offsets written on
-// the device, as the time-sliced finder's window events are). With
-// ws_only, the call stops after the finder: every event's candidates and
-// hit lists stay in w (cand_ws at offsets[e] / T, hits_ws at offsets[e],
-// ev_ncand, and the status in w.err, which the caller clears), a one-event
-// call included; cand, hit_index and counts are not used.
+// longest events first (an ordering kernel ahead of the finder).
 hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events, int64_t n_total,
                           const int64_t *offsets, const float *z, const int16_t *vane, int32_t max_iters,
                           hough_candidate *cand, int32_t *hit_index, int64_t *counts, bool timed,
-                          bool longest_first, bool total_is_bound = false, bool ws_only = false);
+                          bool longest_first);
+// The finder's arguments of context c on workspace w, but for the call's events,
+// hits and outputs.
+FindArgs find_args(const Ctx &c, const Workspace &w);
 
 }  // namespace rt
 }  // namespace hough

@@ -121,3 +121,56 @@ def test_invalid_hits_reported(gpu_available):
         assert info["detail"] == first, (what, info["detail"], first)
     # the context works normally afterwards
     check(b, "after errors")
+
+
+def test_windows_past_the_staged_size(gpu_available):
+    # windows of more hits than the workgroup stages in LDS (about 2400 in the
+    # coarse-to-fine mode): carried tracks and seeds read them in device memory
+    b = eventgen.timeline_batch(2, 6.0, 200.0, seed0=1600)
+    first = b.t[:b.offsets[1]]
+    assert np.sum((first >= 80.0) & (first < 160.0)) > 2450
+    tracks, _, info = check(b, "large windows", tw_kw={"window_ns": 80.0, "step_ns": 10.0, "gate_t_ns": 8.0},
+                            n_theta=180, n_rho=1000, peak_mode=2, min_votes=5)
+    assert info["continued"] > 0 and len(tracks) > 0
+
+
+def test_coarse_to_fine_windows(gpu_available):
+    b = eventgen.timeline_batch(3, 6.0, 40.0, seed0=1650)
+    tracks, _, _ = check(b, "coarse-to-fine seeds", n_theta=180, n_rho=1000, peak_mode=2)
+    assert len(tracks) > 0
+
+
+@pytest.mark.parametrize("n_vanes", [64, 65, 1000])
+def test_vane_counts_around_a_wave(gpu_available, n_vanes):
+    # the seed's vane table is walked 64 vanes at a time
+    b = eventgen.timeline_batch(2, 6.0, 30.0, seed0=1700)
+    check(b, "%d vanes" % n_vanes, n_vanes=n_vanes)
+
+
+def test_sparse_timelines_skip_empty_windows(gpu_available):
+    # long stretches without a hit, hits at a timeline's start and end, and
+    # more windows than the hits reach
+    tls = [eventgen.make_timeline(1800, 0.0008, 40000.0), eventgen.make_timeline(1801, 0.05, 300.0),
+           eventgen.make_timeline(1802, 0.0001, 40000.0)]
+    b = eventgen.make_timeline_batch(tls)
+    check(b, "sparse", n_windows=b.n_windows() + 500)
+    check(b, "sparse, odd steps", tw_kw={"window_ns": 7.3, "step_ns": 2.9})
+    check(b, "sparse, seeds of three hits", min_votes=3)
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 128])
+def test_windows_of_whole_waves(gpu_available, n):
+    # a window's hits at and around the 64 the quiet-window scan holds, on exact curves
+    from test_tw_oracle import curve
+    parts = []
+    for k in range(-(-n // 8)):
+        m = min(8, n - 8 * k)
+        r, z, v, t = curve(m, v0=(5 * k) % 32, dt=0.1, t0=0.05 + 0.11 * k)
+        parts.append((np.asarray(r) + 3.0 * (k % 7), np.asarray(z) + 5.0 * k - 60.0, v, t))
+    r, z, v, t = (np.concatenate([np.asarray(p[i]) for p in parts]) for i in range(4))
+    order = np.argsort(t, kind="stable")
+    tl = eventgen.Timeline(r=r[order].astype(np.float32), z=z[order].astype(np.float32), vane=v[order].astype(np.int16),
+                           t=t[order].astype(np.float32), track=np.zeros(n, np.int32), seed=0, rate_per_ns=0.0,
+                           span_ns=0.0, t_decay=np.zeros(1), p=np.zeros(1))
+    assert tl.t.max() < 10.0
+    check(eventgen.make_timeline_batch([tl]), "%d hits" % n, n_windows=4)
