@@ -35,6 +35,7 @@
 #include "hough_wave.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace hough {
 
@@ -358,6 +359,7 @@ struct Shared {
     int bad;
     unsigned long long maxdrop;
     unsigned long long best;
+    unsigned long long amax[2];  // argmax_loop: largest key of the current and the next iteration
     int wtot[16];
     int n_trunc;     // peak-list truncations (diagnostics)
     int n_hotscan;   // hot-list overflow scans (diagnostics)
@@ -767,10 +769,10 @@ __device__ __forceinline__ void hash_insert(const unsigned long long *hs, int n_
 // Peaks among the n_hs hot bins (keys in L.hs): the window test looks the
 // neighbours up in an LDS hash table keyed by flat index (bins below T are
 // absent and count as 0). Leaves the peak keys sorted in descending order in
-// L.hs and returns their number.
-template <int NT>
+// L.sorted and returns their number. MAX: the largest key alone.
+template <int NT, bool MAX>
 __device__ __forceinline__ int hotset_peaks(const FindArgs &A, const Lds &L, int n_hs, Shared &sh) {
-    if (A.peak_mode == 0) {
+    if constexpr (MAX) {
         if (tid_x() == 0) sh.best = 0ull;
         __syncthreads();
         // the largest key: per thread, per wave (DPP), then one LDS atomic
@@ -2280,6 +2282,133 @@ __device__ __forceinline__ void associate(const FindArgs &A, const float2 *__res
 }
 
 
+// LDS words that argmax_loop needs ahead of the hot set: the (cos, sin) table
+// and one register batch of removed hits.
+__device__ __forceinline__ bool argmax_loop_fits(const FindArgs &A) {
+    return 8 * A.n_theta + 8 * kChunks * kWave <= A.hs_off;
+}
+
+// The rest of an argmax event once its hot set is in LDS (L.hs, n_hs entries)
+// and its alive hits in registers: per iteration the largest key is the peak,
+// every alive hit on its line is claimed, and the claimed hits' votes are taken
+// out of the hot bins' counts. Removing hits never raises a count, so the hot
+// set stays complete, and a bin's count is exactly that of the hits left.
+//
+// Bound by the chain of one peak after another: two barriers an iteration.
+// Each wave holds every alive hit, so each finds the peak's matches itself,
+// and a hot bin (one lane each) is tested against the 8 or so removed hits
+// instead of recounted over the 200 alive ones; the alive list is not rebuilt. As
+// iterations of the general loop (recount, peak search, alive list and association,
+// about 15 barriers) an event of 50 tracks on 180 x 1000 bins took 28 k cycles for
+// each of its 15.6 peaks; here about 3 k (1024 such events 862 -> 221 us).
+// The candidates' bin centres are filled in at the end. Returns the iterations.
+template <int NT>
+__device__ __forceinline__ int argmax_loop(const FindArgs &A, const float2 *__restrict__ cs, int e, int64_t b, int iter,
+                                           const Lds &L, const HitRegs &h, int n_alive, int n_hs, bool small,
+                                           Shared &sh, unsigned long long &evals, int &recounts) {
+    constexpr int NW = NT / kWave;
+    const int wave = wave_id();
+    const int lane = lane_id();
+    const int64_t cbase = b / (int64_t)A.min_votes;
+    float2 *const ctab = reinterpret_cast<float2 *>(L.tile);
+    float2 *const rem = ctab + A.n_theta;
+    for (int j = tid_x(); j < A.n_theta; j += NT) ctab[j] = cs[j];
+    if (tid_x() < 2) sh.amax[tid_x()] = 0ull;
+    __syncthreads();
+    const int ncand0 = sh.ncand;
+    int ncand = ncand0, nhit = sh.nhit;
+    unsigned long long alive[kChunks];
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c)
+        alive[c] = uniform64(__ballot(c * kWave + lane < n_alive));
+    int side = 0, nrem = 0;
+    for (;; ++iter) {
+        // counts without the hits removed last, and the largest key
+        unsigned long long top = 0ull;
+        for (int x = tid_x(); x < n_hs; x += NT) {
+            unsigned long long key = L.hs[x];
+            if (key != 0ull && nrem > 0) {
+                const uint32_t flat = 0xffffffffu - (uint32_t)key;
+                const int j = (int)(flat / (uint32_t)A.n_rho);
+                const int k = (int)(flat - (uint32_t)j * (uint32_t)A.n_rho);
+                const float2 t = ctab[j];
+                uint32_t cnt = (uint32_t)(key >> 32);
+                for (int r = 0; r < nrem; ++r) {
+                    const float2 pz = rem[r];
+                    cnt -= rho_bin(pz.x, pz.y, t.x, t.y, A.rho_min, A.inv_w) == k ? 1u : 0u;
+                }
+                key = cnt >= A.min_votes ? bin_key(cnt, flat) : 0ull;
+                L.hs[x] = key;
+            }
+            top = key > top ? key : top;
+        }
+        top = wave_max64(top);
+        if (lane == 0 && top != 0ull) atomicMax(&sh.amax[side], top);
+        __syncthreads();
+        top = uniform64(sh.amax[side]);
+        if (top == 0ull) break;
+        // the peak's matches, the same masks in every wave
+        const uint32_t flat = 0xffffffffu - (uint32_t)top;
+        const int jp = (int)(flat / (uint32_t)A.n_rho);
+        const int kp = (int)(flat - (uint32_t)jp * (uint32_t)A.n_rho);
+        const float2 t = ctab[jp];
+        const float lo = (float)(kp - A.assoc_window), hi = (float)(kp + A.assoc_window + 1);
+        nrem = 0;
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) {
+            if (c >= h.nch) break;
+            const unsigned long long m =
+                __ballot(rho_in(h.phi[c], h.z[c], t.x, t.y, A.rho_min, A.inv_w, lo, hi)) & alive[c];
+            alive[c] &= ~m;
+            if (c % NW == wave && ((m >> lane) & 1ull)) {
+                const int at = nrem + mbcnt64(m);
+                const int q = c * kWave + lane;
+                const int il = small ? (int)sh.aidx_s[q] : A.aidx[b + q];
+                rem[at] = make_float2(h.phi[c], h.z[c]);
+                A.hits_ws[b + nhit + at] = il;
+                A.state[b + il] = ncand;
+            }
+            nrem += __popcll(m);
+        }
+        if (tid_x() == 0) {
+            hough_candidate cd;
+            cd.event = e;
+            cd.iter = iter;
+            cd.theta_bin = jp;
+            cd.rho_bin = kp;
+            cd.peak_votes = (uint32_t)(top >> 32);
+            cd.n_hits = (uint32_t)nrem;
+            cd.hit_offset = nhit;
+            cd.theta = 0.0f;
+            cd.rho = 0.0f;
+            A.cand_ws[cbase + ncand] = cd;
+            sh.amax[side ^ 1] = 0ull;
+        }
+        ++ncand;
+        nhit += nrem;
+        n_alive -= nrem;
+        side ^= 1;
+        __syncthreads();
+        if ((A.max_iters > 0 && iter + 1 >= A.max_iters) || n_alive < (int)A.min_votes) {
+            ++iter;
+            break;
+        }
+        evals += (unsigned long long)nrem * (unsigned long long)n_hs;
+        ++recounts;
+    }
+    for (int i = ncand0 + (int)tid_x(); i < ncand; i += NT) {
+        hough_candidate *const cd = A.cand_ws + cbase + i;
+        cd->theta = A.theta_c[cd->theta_bin];
+        cd->rho = A.rho_c[cd->rho_bin];
+    }
+    if (tid_x() == 0) {
+        sh.ncand = ncand;
+        sh.nhit = nhit;
+    }
+    __syncthreads();
+    return iter;
+}
+
 __device__ void write_error_counts(int64_t *counts, long long status, long long detail) {
     counts[HOUGH_COUNT_CANDIDATES] = 0;
     counts[HOUGH_COUNT_HITS] = 0;
@@ -2335,8 +2464,11 @@ __device__ __forceinline__ Lds find_lds(const FindArgs &A) {
 }
 
 // The whole find-and-remove loop of event e, whose n64 hits start at b, by the
-// workgroup (b and n64 uniform, in scalar registers).
-template <int NT>
+// workgroup (b and n64 uniform, in scalar registers). MAX: the configuration
+// searches the largest bin (peak_mode 0), else every local maximum (1); one
+// kernel for both held registers of the one in the loops of the other (Poisson(20)
+// batch 699 -> 723 us with argmax_loop beside the window test).
+template <int NT, bool MAX>
 __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__restrict__ cs, const Lds &L, Shared &sh,
                                            int e, int64_t b, int64_t n64) {
     constexpr int NW = NT / kWave;
@@ -2593,8 +2725,13 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                     votes += (unsigned long long)n_alive * (unsigned long long)A.n_theta;
                 }
                 HOUGH_PHASE_MARK(kPhSweep);
+                if (MAX && hs_valid && argmax_loop_fits(A)) {
+                    iter = argmax_loop<NT>(A, cs, e, b, iter, L, h, n_alive, n_hs, small, sh, evals, recounts);
+                    HOUGH_PHASE_MARK(kPhAssoc);
+                    break;
+                }
                 if (hs_valid) {
-                    const int npk = hotset_peaks<NT>(A, L, n_hs, sh);
+                    const int npk = hotset_peaks<NT, MAX>(A, L, n_hs, sh);
                     HOUGH_PHASE_MARK(kPhPeaks);
                     if (npk >= 0) {
                         done = true;
@@ -2643,7 +2780,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                     votes += (unsigned long long)n_alive * (unsigned long long)A.n_theta;
                     int npk = -1;
                     if (sh.big_ovf == 0) {
-                        if (A.peak_mode == 0) {
+                        if (MAX) {
                             const unsigned long long best = sh.best;
                             if (tid_x() == 0) S.srt[0] = best;
                             sync_global();
@@ -2693,7 +2830,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
             __syncthreads();
             sweep<NT>(A, cs, b, L, h, nbatch, ceil_key, sh);
             int npk;
-            if (A.peak_mode == 0) {
+            if (MAX) {
                 const unsigned long long best = sh.best;
                 npk = (uint32_t)(best >> 32) >= A.min_votes ? 1 : 0;
                 __syncthreads();
@@ -2769,29 +2906,39 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // the event's bounds are uniform: keep them (and every address derived
     // from them) in scalar registers
     const int64_t b = uniform64(A.offsets[e]);
-    find_event<NT>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
+    find_event<NT, false>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
+}
+
+// The same for peak_mode 0.
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_argmax(FindArgs A,
+                                                                                     const float2 *__restrict__ cs) {
+    __shared__ Shared sh;
+    const int e = A.order != nullptr ? __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]) : (int)blockIdx.x;
+    const int64_t b = uniform64(A.offsets[e]);
+    find_event<NT, true>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
 }
 
 // The event finder as a call: inlined into the window loop below, the values
 // that the compiler keeps over the loop took 1136 B of scratch a lane; the call
 // saves and restores 20 registers instead. *A is read with scalar loads, like a
 // kernel's arguments (vector loads held in registers: 480 B).
-template <int NT>
+template <int NT, bool MAX>
 __device__ __noinline__ void find_event_call(const FindArgs *A, int e, int64_t b, int64_t n) {
     __shared__ Shared sh;
     const FindArgs &a = tw::const_args(A);
-    find_event<NT>(a, a.cs, find_lds(a), sh, __builtin_amdgcn_readfirstlane(e), uniform64(b), uniform64(n));
+    find_event<NT, MAX>(a, a.cs, find_lds(a), sh, __builtin_amdgcn_readfirstlane(e), uniform64(b), uniform64(n));
 }
 
 // The window loop of the time-sliced finder: one workgroup per timeline, which
 // runs find_event on each window that needs it (see hough_tw.h). Workgroups of
 // the finder's own shape, so no more are resident at once than it has
 // large-event slots.
-template <int NT>
+template <int NT, bool MAX>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_tw_run(TwArgs W) {
     __shared__ tw::Shared T;
     tw::run<NT>(W, tw::const_args(W.find), g_lds, T,
-                [&](int e, int64_t b, int64_t n) { find_event_call<NT>(W.find, e, b, n); });
+                [&](int e, int64_t b, int64_t n) { find_event_call<NT, MAX>(W.find, e, b, n); });
 }
 
 // First histogram sweep of each event split over `groups` workgroups: group g
@@ -3303,45 +3450,49 @@ hipError_t find_blocks_per_cu(int wg_threads, int lds_bytes, int *blocks) {
     }
 }
 
-hipError_t set_find_lds_limit(int wg_threads, int lds_bytes) {
+namespace {
+// f(std::integral_constant<int, NT>) for the workgroup sizes there are.
+template <typename F>
+hipError_t with_threads(int wg_threads, F f) {
     switch (wg_threads) {
     case 256:
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(k_find<256>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        return f(std::integral_constant<int, 256>());
     case 512:
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(k_find<512>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        return f(std::integral_constant<int, 512>());
     case 1024:
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(k_find<1024>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        return f(std::integral_constant<int, 1024>());
     default:
         return hipErrorInvalidValue;
     }
+}
+
+hipError_t lds_limit(const void *f, int lds_bytes) {
+    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+}
+}  // namespace
+
+hipError_t set_find_lds_limit(int wg_threads, int lds_bytes) {
+    return with_threads(wg_threads, [&](auto nt) {
+        const hipError_t e = lds_limit(reinterpret_cast<const void *>(k_find<nt()>), lds_bytes);
+        return e != hipSuccess ? e : lds_limit(reinterpret_cast<const void *>(k_argmax<nt()>), lds_bytes);
+    });
 }
 
 hipError_t set_tw_lds_limit(int wg_threads, int lds_bytes) {
-    const void *f = wg_threads == 256   ? reinterpret_cast<const void *>(k_tw_run<256>)
-                    : wg_threads == 512 ? reinterpret_cast<const void *>(k_tw_run<512>)
-                                        : reinterpret_cast<const void *>(k_tw_run<1024>);
-    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    return with_threads(wg_threads, [&](auto nt) {
+        const hipError_t e = lds_limit(reinterpret_cast<const void *>(k_tw_run<nt(), false>), lds_bytes);
+        return e != hipSuccess ? e : lds_limit(reinterpret_cast<const void *>(k_tw_run<nt(), true>), lds_bytes);
+    });
 }
 
-hipError_t launch_tw_run(const TwArgs &t, int wg_threads, int lds_bytes, hipStream_t s) {
-    const dim3 grid(t.n_tl);
-    switch (wg_threads) {
-    case 256:
-        hipLaunchKernelGGL(k_tw_run<256>, grid, dim3(256), lds_bytes, s, t);
-        break;
-    case 512:
-        hipLaunchKernelGGL(k_tw_run<512>, grid, dim3(512), lds_bytes, s, t);
-        break;
-    case 1024:
-        hipLaunchKernelGGL(k_tw_run<1024>, grid, dim3(1024), lds_bytes, s, t);
-        break;
-    default:
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+hipError_t launch_tw_run(const TwArgs &t, int wg_threads, bool argmax, int lds_bytes, hipStream_t s) {
+    return with_threads(wg_threads, [&](auto nt) {
+        if (argmax)
+            hipLaunchKernelGGL((k_tw_run<nt(), true>), dim3(t.n_tl), dim3(nt()), lds_bytes, s, t);
+        else
+            hipLaunchKernelGGL((k_tw_run<nt(), false>), dim3(t.n_tl), dim3(nt()), lds_bytes, s, t);
+        return hipGetLastError();
+    });
 }
 
 hipError_t set_dump_lds_limit(int lds_bytes) {
@@ -3351,21 +3502,13 @@ hipError_t set_dump_lds_limit(int lds_bytes) {
 
 hipError_t launch_find(const FindArgs &a, int wg_threads, int lds_bytes, hipStream_t s) {
     if (a.n_events <= 0) return hipSuccess;
-    dim3 grid(a.n_events);
-    switch (wg_threads) {
-    case 256:
-        hipLaunchKernelGGL(k_find<256>, grid, dim3(256), lds_bytes, s, a, a.cs);
-        break;
-    case 512:
-        hipLaunchKernelGGL(k_find<512>, grid, dim3(512), lds_bytes, s, a, a.cs);
-        break;
-    case 1024:
-        hipLaunchKernelGGL(k_find<1024>, grid, dim3(1024), lds_bytes, s, a, a.cs);
-        break;
-    default:
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return with_threads(wg_threads, [&](auto nt) {
+        if (a.peak_mode == 0)
+            hipLaunchKernelGGL(k_argmax<nt()>, dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
+        else
+            hipLaunchKernelGGL(k_find<nt()>, dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s) {

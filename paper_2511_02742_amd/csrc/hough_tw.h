@@ -46,7 +46,7 @@ struct TwArgs {
 
 // The window loop of every timeline (one workgroup each): hough_kernels.hip
 // with the histogram finder, hough_cf.hip with the coarse-to-fine one.
-hipError_t launch_tw_run(const TwArgs &t, int wg_threads, int lds_bytes, hipStream_t s);
+hipError_t launch_tw_run(const TwArgs &t, int wg_threads, bool argmax, int lds_bytes, hipStream_t s);
 hipError_t set_tw_lds_limit(int wg_threads, int lds_bytes);
 hipError_t launch_tw_run_cf(const TwArgs &t, int wg_threads, int lds_bytes, hipStream_t s);
 hipError_t set_tw_cf_lds_limit(int wg_threads, int lds_bytes);

@@ -323,7 +323,7 @@ hough_status hough_tw_find(hough_ctx *ctx, void *stream, const hough_tw_config *
         hipLaunchKernelGGL(k_tw_validate, dim3((unsigned)B), dim3(256), 0, s, A);
         if ((st = launched("k_tw_validate"))) return st;
         const hipError_t e = c->cfg.peak_mode == 2 ? launch_tw_run_cf(A, c->wg_threads, c->tw_lds, s)
-                                                   : launch_tw_run(A, c->wg_threads, c->tw_lds, s);
+                                                   : launch_tw_run(A, c->wg_threads, c->cfg.peak_mode == 0, c->tw_lds, s);
         if (e != hipSuccess)
             return fail(c, HOUGH_ERR_DEVICE, std::string("k_tw_run launch failed: ") + hipGetErrorString(e));
     }

@@ -608,3 +608,34 @@ def test_vote_count_is_the_sweeps(gpu_available):
     f = finder()
     _, _, info = run_batch(f, b)
     assert info["votes"] >= b.n_hits * f.config.n_theta and info["votes"] <= info["evals"]
+
+
+@pytest.mark.parametrize("kw", [{}, {"assoc_window": 2}, {"max_iters": 1}, {"max_iters": 7}, {"min_votes": 3},
+                                {"wg_threads": 256}, {"wg_threads": 512, "tile_rows": 14}, {"n_theta": 180, "n_rho": 1000},
+                                {"n_theta": 9000, "n_rho": 256, "min_votes": 9}])
+def test_argmax_peak_after_peak(gpu_available, kw):
+    # one peak an iteration from the hot set's running counts: hit counts at
+    # the edges of the 64-hit chunks and of the register batch, hot sets of more bins than
+    # threads (small T), iteration caps, and a theta table the LDS does not
+    # hold beside the row buffers (9000 rows: the general loop). The claimed hits
+    # of an iteration can be the chunk's last ones or all there are.
+    sizes = [5, 6, 63, 64, 65, 128, 129, 448, 511, 512, 513, 640]
+    evs = []
+    for i, n in enumerate(sizes):
+        ev = eventgen.pileup_event(52_000 + i, n_tracks=n // 3 + 12)
+        assert ev.n_hits >= n
+        evs.append((ev.z[:n], ev.vane[:n]))
+    # a few lines of exactly T hits and one of many
+    for n in (6, 70):
+        evs.append((np.linspace(-40.0, 40.0, n).astype(np.float32), np.full(n, 7, np.int16)))
+    if kw.get("n_theta") == 9000 or kw.get("min_votes") == 3:
+        evs = evs[:9]
+    off = np.concatenate([[0], np.cumsum([len(z) for z, _ in evs])]).astype(np.int64)
+    b = eventgen.Batch(r=np.zeros(off[-1], np.float32), z=np.concatenate([z for z, _ in evs]),
+                       vane=np.concatenate([v for _, v in evs]), offsets=off, events=[])
+    got, want = check_batch(b, "argmax %s" % kw, peak_mode=0, **kw)
+    assert len(want.cand) > len(evs) // 2
+    # alone, with the first sweep split over several workgroups
+    for z, v in evs[:4]:
+        one = eventgen.Batch(r=np.zeros(len(z), np.float32), z=z, vane=v, offsets=np.array([0, len(z)], np.int64), events=[])
+        check_batch(one, "argmax alone %s" % kw, peak_mode=0, **kw)
