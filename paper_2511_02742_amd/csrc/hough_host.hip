@@ -74,6 +74,26 @@ constexpr int kOrderMin = 64;           // calls of more events than this (and t
 constexpr int kSingleSweepGroups = 32;
 constexpr int kSingleSweepThreads = 256;
 constexpr int kSmallCall = 8;
+// The dense shape: workgroups of 512 threads on half the LDS, two events per CU,
+// so that one event's chains of dependent steps overlap the other's sweep. An
+// event takes longer in it, and its shorter lists send more events to the
+// large-event path, whose length ends the call: it pays once the events outnumber
+// the workgroups. Against the default shape, ratio of times (1024 x 1024 bins):
+//   27 hits per event     1.18 at 512 events, 1.36 at 1024, 1.46 at 4096
+//   110 hits (Poisson)    0.80 at 384, 1.3 at 768, 1.48 at 4096
+//   275 hits              0.75 at 1024, 1.0 at 2048, 1.33 at 3072
+//   550 hits              1.06 at 768, 1.4 at 3072
+//   1 to 100 tracks mixed 0.83 at 1024, 1.2 at 2048 and 3072, 1.39 at 4096
+// and on 180 rows, where few bins reach T, with 275 hits 1.38 (every local
+// maximum) and 1.5 (largest bin) at 768 events. With fewer than kDenseRho rho
+// bins more bins reach T than its hot set holds (512 x 512 bins, 110 hits: 0.5 at
+// 768 events, 0.9 at 2048).
+constexpr int kDenseThreads = 512;
+constexpr int kDenseRho = 1000;
+constexpr int kDenseMany = 3072;          // events from which on it is taken for any size of event
+constexpr int kDenseEvents = 768;         // and for events of few hits and votes:
+constexpr int kDenseHits = 320;
+constexpr int kDenseVotes = 140000;       // hits times theta rows
 constexpr int kBandCall = 64;             // calls of up to this many events may run k_band
 constexpr int kTwCfLds = 48 << 10;        // LDS the time-sliced finder takes at least in mode 2 (windows of about 2000 hits)
 constexpr int64_t kRegisterHits = 512;    // alive hits the finder holds in registers
@@ -183,25 +203,22 @@ void build_tables(Ctx &c) {
     }
 }
 
-// Picks the LDS tile: the own theta rows plus the 2w halo rows make a
-// multiple of the waves per workgroup (each wave owns whole rows), as many as
-// fit the per-workgroup LDS next to the hot list and the peak lists.
-hough_status choose_shape(Ctx &c, std::string &why) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, c.device) != hipSuccess) { why = "hipGetDeviceProperties failed"; return HOUGH_ERR_DEVICE; }
-    const int lds_max = (int)prop.sharedMemPerBlock;
+// The shape of `threads` per workgroup with LDS tiles of tile_rows own rows (0:
+// as many as fit, in multiples of the waves together with the 2w halo rows, since
+// each wave owns whole rows) in lds_max bytes, next to the hot list and the
+// peak lists.
+hough_status make_shape(const Ctx &c, int threads, int tile_rows, int lds_max, int n_cu, Shape &f, std::string &why) {
     const hough_config &g = c.cfg;
-    c.wg_threads = g.wg_threads > 0 ? g.wg_threads : 1024;
-    const int nw = c.wg_threads / 64;
-    c.pitch = (g.n_rho + 3) & ~3;
+    f.wg_threads = threads;
+    const int nw = f.wg_threads / 64;
     const int halo = g.peak_mode == 1 ? g.nms_radius : 0;
-    const int extra = hough::find_lds_extra(c.wg_threads, kHotCap, kPeakKeep) + kStaticLds;
+    const int extra = hough::find_lds_extra(f.wg_threads, kHotCap, kPeakKeep) + kStaticLds;
     const int row_bytes = 4 * c.pitch;
     const int total_fit = (lds_max - extra) / row_bytes;
     if (total_fit - 2 * halo < 1) { why = "n_rho too large for the LDS tile"; return HOUGH_ERR_INVALID_ARG; }
     int rows;
-    if (g.tile_rows > 0) {
-        rows = g.tile_rows;
+    if (tile_rows > 0) {
+        rows = tile_rows;
     } else {
         int total = (total_fit / nw) * nw;
         if (total - 2 * halo < 1) total = total_fit;
@@ -209,62 +226,80 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     }
     rows = std::min(rows, g.n_theta);
     if (rows + 2 * halo > total_fit) { why = "tile_rows does not fit in LDS"; return HOUGH_ERR_INVALID_ARG; }
-    c.tile_rows = rows;
+    f.tile_rows = rows;
     // the association scratch reuses the tile: one peak per pass must fit
     // at every event size up to the largest
     int assoc_min = 0;
     for (int w = 1; w <= HOUGH_MAX_EVENT_HITS / 64; ++w)
         assoc_min = std::max(assoc_min, hough::assoc_fixed_bytes(w) + hough::assoc_peak_bytes(w));
-    c.tile_bytes = std::max(row_bytes * (rows + 2 * halo), assoc_min);
-    c.tile_bytes = (c.tile_bytes + 15) & ~15;
-    c.lds_bytes = c.tile_bytes + hough::find_lds_extra(c.wg_threads, kHotCap, kPeakKeep);
-    if (c.lds_bytes + kStaticLds > lds_max) { why = "LDS budget exceeded"; return HOUGH_ERR_INVALID_ARG; }
-    if (hough::set_find_lds_limit(c.wg_threads, c.lds_bytes) != hipSuccess) {
+    f.tile_bytes = std::max(row_bytes * (rows + 2 * halo), assoc_min);
+    f.tile_bytes = (f.tile_bytes + 15) & ~15;
+    f.lds_bytes = f.tile_bytes + hough::find_lds_extra(f.wg_threads, kHotCap, kPeakKeep);
+    if (f.lds_bytes + kStaticLds > lds_max) { why = "LDS budget exceeded"; return HOUGH_ERR_INVALID_ARG; }
+    if (hough::set_find_lds_limit(f.wg_threads, f.lds_bytes) != hipSuccess) {
         why = "hipFuncSetAttribute failed for the finder kernel";
         return HOUGH_ERR_DEVICE;
     }
-    {
-        int per_cu = 0;
-        if (hough::find_blocks_per_cu(c.wg_threads, c.lds_bytes, &per_cu) != hipSuccess || per_cu < 1) {
-            why = "occupancy query failed for the finder kernel";
-            return HOUGH_ERR_DEVICE;
-        }
-        c.max_resident = per_cu * prop.multiProcessorCount;
+    int per_cu = 0;
+    if (hough::find_blocks_per_cu(f.wg_threads, f.lds_bytes, &per_cu) != hipSuccess || per_cu < 1) {
+        why = "occupancy query failed for the finder kernel";
+        return HOUGH_ERR_DEVICE;
     }
+    f.max_resident = per_cu * n_cu;
     // row-stream layout inside the tile: one row buffer per wave (reused by
     // the hash table of the window test: a power-of-two slot count of 8 B,
     // at most half full), then the hot set, then the sorted peak keys
-    {
-        const int rb = (c.wg_threads / 64) * c.pitch * 4;
-        const int sorted_bytes = 8 * (kPeakKeep + kHotCap);
-        int slots = 1;
-        while (2 * slots * 8 <= rb) slots *= 2;
-        int cap = std::min(4096, slots / 2);
-        cap = std::min(cap, (c.tile_bytes - rb - sorted_bytes) / 8);
-        // the row-stream path (up to 512 register-resident alive hits plus
-        // hs_cap more in LDS for a large event) runs the association inside
-        // the row buffers, two peaks per pass at least
-        int assoc_stream = 0;
-        for (int w = 1; w <= (512 + std::max(cap, 0) + 63) / 64; ++w)
-            assoc_stream = std::max(assoc_stream, hough::assoc_fixed_bytes(w) + 2 * hough::assoc_peak_bytes(w));
-        // a large event's count histogram and scatter cursors (one int each
-        // per possible count) also sit in the row buffers
-        const int count_sort = 8 * (512 + std::max(cap, 0) + 1);
-        c.stream_ok = cap >= 256 && rb >= assoc_stream && rb >= count_sort ? 1 : 0;
-        c.hs_cap = std::max(cap, 0);
-        c.hs_off = rb;
-        c.sorted_off = rb + 8 * c.hs_cap;
-        // large events: device-memory hot set and hash table, and a peak
-        // list the row buffers can sort (a power of two of u64 keys)
-        c.big_pk = 32768;
-        c.big_sort = 1;
-        while (2 * c.big_sort * 8 <= rb) c.big_sort *= 2;
-        // the banded sweep's row lists (2 w + 1 per wave) after the sorted
-        // peak keys, at least 32 entries each
-        c.roll_off = c.sorted_off;
-        c.roll_bytes = c.tile_bytes - c.roll_off;
-        const int nl = 2 * g.nms_radius + 1;
-        c.big_ok = c.stream_ok && c.roll_bytes >= 4 * nl * (c.wg_threads / 64) * 32 ? 1 : 0;
+    const int rb = (f.wg_threads / 64) * c.pitch * 4;
+    const int sorted_bytes = 8 * (kPeakKeep + kHotCap);
+    int slots = 1;
+    while (2 * slots * 8 <= rb) slots *= 2;
+    int cap = std::min(4096, slots / 2);
+    cap = std::min(cap, (f.tile_bytes - rb - sorted_bytes) / 8);
+    // the row-stream path (up to 512 register-resident alive hits plus
+    // hs_cap more in LDS for a large event) runs the association inside
+    // the row buffers, two peaks per pass at least
+    int assoc_stream = 0;
+    for (int w = 1; w <= (512 + std::max(cap, 0) + 63) / 64; ++w)
+        assoc_stream = std::max(assoc_stream, hough::assoc_fixed_bytes(w) + 2 * hough::assoc_peak_bytes(w));
+    // a large event's count histogram and scatter cursors (one int each
+    // per possible count) also sit in the row buffers
+    const int count_sort = 8 * (512 + std::max(cap, 0) + 1);
+    f.stream_ok = cap >= 256 && rb >= assoc_stream && rb >= count_sort ? 1 : 0;
+    f.hs_cap = std::max(cap, 0);
+    f.hs_off = rb;
+    f.sorted_off = rb + 8 * f.hs_cap;
+    // large events: a peak list that the row buffers can sort (a power of two
+    // of u64 keys)
+    f.big_sort = 1;
+    while (2 * f.big_sort * 8 <= rb) f.big_sort *= 2;
+    // the banded sweep's row lists (2 w + 1 per wave) after the sorted
+    // peak keys, at least 32 entries each
+    f.roll_off = f.sorted_off;
+    f.roll_bytes = f.tile_bytes - f.roll_off;
+    const int nl = 2 * g.nms_radius + 1;
+    f.big_ok = f.stream_ok && f.roll_bytes >= 4 * nl * (f.wg_threads / 64) * 32 ? 1 : 0;
+    return HOUGH_OK;
+}
+
+// The configuration's shape, or the default one: the largest workgroup and the
+// whole LDS. Beside the default, the dense shape for calls of many events.
+hough_status choose_shape(Ctx &c, std::string &why) {
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, c.device) != hipSuccess) { why = "hipGetDeviceProperties failed"; return HOUGH_ERR_DEVICE; }
+    const int lds_max = (int)prop.sharedMemPerBlock;
+    const int n_cu = prop.multiProcessorCount;
+    const hough_config &g = c.cfg;
+    c.pitch = (g.n_rho + 3) & ~3;
+    c.big_pk = 32768;
+    const int row_bytes = 4 * c.pitch;
+    hough_status st = make_shape(c, g.wg_threads > 0 ? g.wg_threads : 1024, g.tile_rows, lds_max, n_cu, c, why);
+    if (st) return st;
+    if (g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2 && g.n_rho >= kDenseRho) {
+        std::string none;
+        Shape f;
+        if (make_shape(c, kDenseThreads, 0, lds_max / 2, n_cu, f, none) == HOUGH_OK && f.stream_ok && f.big_ok &&
+            f.max_resident >= 2 * n_cu)
+            c.dense = f;
     }
     // |rho| <= r (1 + 2^-24)^3 for r = sqrt(phi^2 + z^2); a rho at least
     // delta inside [rho_min, rho_max] gives a bin in [0, n_rho) after the
@@ -350,7 +385,14 @@ void free_workspace(Workspace &w) {
     w = Workspace();
 }
 
-size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, char *base, Workspace *w) {
+// Whether a call of n_events events with n_hits hits in all takes the dense shape.
+bool takes_dense(const Ctx &c, int64_t n_events, int64_t n_hits) {
+    if (c.dense.max_resident == 0 || n_events < kDenseEvents) return false;
+    return n_events >= kDenseMany ||
+           (n_hits <= kDenseHits * n_events && n_hits * c.cfg.n_theta <= kDenseVotes * n_events);
+}
+
+size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, char *base, Workspace *w, bool dense) {
     const int64_t ncand = nh / (int64_t)c.cfg.min_votes + 1;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
@@ -364,7 +406,8 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
     const size_t o_ghs = ghs_events > 0 ? take(8 * (size_t)ghs_events * (size_t)std::max(c.hs_cap, 1)) : 0;
     // large-event slots: no more workgroups than events, nor than fit the
     // device at once, hold one at a time
-    const int32_t slots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(ne, std::max(c.max_resident, 1)));
+    const int resident = dense ? std::max(c.max_resident, c.dense.max_resident) : c.max_resident;
+    const int32_t slots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(ne, std::max(resident, 1)));
     const int64_t slot_bytes = (int64_t)align256(8 * 2 * (size_t)big_pk);
     const size_t o_pflags = take(4 * ((size_t)slots + 2 * kBandCall));
     const size_t o_bcnt = take(4 * (size_t)kBandCall * 16);
@@ -415,14 +458,20 @@ hough_status ensure_workspace(const Ctx &c, Workspace &w, int64_t n_hits, int64_
         nh = std::max<int64_t>(nh, w.hits + w.hits / 2);
         ne = std::max<int64_t>(ne, w.events + w.events / 2);
     }
-    const size_t bytes = layout_workspace(c, nh, ne, c.big_pk, nullptr, nullptr);
+    bool dense = c.dense.max_resident > 0 && ne >= kDenseEvents;
     if (w.base) {
         if (hipStreamSynchronize(s) != hipSuccess) return HOUGH_ERR_DEVICE;
         free_workspace(w);
     }
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return HOUGH_ERR_OOM;
-    layout_workspace(c, nh, ne, c.big_pk, static_cast<char *>(p), &w);
+    if (dense && hipMalloc(&p, layout_workspace(c, nh, ne, c.big_pk, nullptr, nullptr, true)) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+        dense = false;   // without its slots: the calls take the default shape
+    }
+    if (p == nullptr && hipMalloc(&p, layout_workspace(c, nh, ne, c.big_pk, nullptr, nullptr)) != hipSuccess)
+        return HOUGH_ERR_OOM;
+    layout_workspace(c, nh, ne, c.big_pk, static_cast<char *>(p), &w, dense);
     // error and split-sweep words start cleared; every call
     // leaves them so
     if (hough::launch_clear_workspace(w.err, w.g_cnt, w.g_flag, ne, w.pool_flags, w.pool_words, s) != hipSuccess)
@@ -430,7 +479,7 @@ hough_status ensure_workspace(const Ctx &c, Workspace &w, int64_t n_hits, int64_
     return HOUGH_OK;
 }
 
-hough::FindArgs find_args(const Ctx &c, const Workspace &w) {
+hough::FindArgs find_args(const Ctx &c, const Shape &f, const Workspace &w) {
     hough::FindArgs a{};
     const hough_config &g = c.cfg;
     a.band_min = (int32_t)kRegisterHits;
@@ -459,16 +508,16 @@ hough::FindArgs find_args(const Ctx &c, const Workspace &w) {
     a.ev_stats = w.ev_stats;
     a.order = nullptr;
     a.err = w.err;
-    a.tile_rows = c.tile_rows;
+    a.tile_rows = f.tile_rows;
     a.pitch = c.pitch;
-    a.tile_bytes = c.tile_bytes;
+    a.tile_bytes = f.tile_bytes;
     a.hcap = kHotCap;
     a.pkeep = kPeakKeep;
-    a.stream_ok = c.stream_ok;
+    a.stream_ok = f.stream_ok;
     a.safe_r2 = c.safe_r2;
-    a.hs_cap = c.hs_cap;
-    a.hs_off = c.hs_off;
-    a.sorted_off = c.sorted_off;
+    a.hs_cap = f.hs_cap;
+    a.hs_off = f.hs_off;
+    a.sorted_off = f.sorted_off;
     a.g_cnt = w.g_cnt;
     a.g_flag = w.g_flag;
     a.g_hs = (c.sweep_groups > 0 && c.stream_ok) ? w.g_hs : nullptr;
@@ -476,10 +525,10 @@ hough::FindArgs find_args(const Ctx &c, const Workspace &w) {
     a.pool_flags = w.pool_flags;
     a.pool_slots = w.pool_slots;
     a.big_pk = w.big_pk;
-    a.big_sort = c.big_sort;
-    a.big_ok = c.big_ok;
-    a.roll_off = c.roll_off;
-    a.roll_bytes = c.roll_bytes;
+    a.big_sort = f.big_sort;
+    a.big_ok = f.big_ok;
+    a.roll_off = f.roll_off;
+    a.roll_bytes = f.roll_bytes;
     a.slot_bytes = w.slot_bytes;
     a.ccs = c.d_ccs;
     a.inv_wc = c.inv_wc;
@@ -498,7 +547,12 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
                           const int64_t *offsets, const float *z, const int16_t *vane, int32_t max_iters,
                           hough_candidate *cand, int32_t *hit_index, int64_t *counts, bool timed,
                           bool longest_first) {
-    hough::FindArgs a = find_args(c, w);
+    // (the served form's launches overlap on the device and keep the default
+    // shape; so does a workspace without a slot for each dense workgroup)
+    const bool dense = longest_first && takes_dense(c, n_events, n_total) &&
+                       w.pool_slots >= std::min<int64_t>(n_events, c.dense.max_resident);
+    const Shape &f = dense ? c.dense : c;
+    hough::FindArgs a = find_args(c, f, w);
     a.n_events = n_events;
     a.n_total = n_total;
     a.offsets = offsets;
@@ -537,10 +591,10 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
         a.b_slot = w.b_slot;
         a.b_cnt = w.b_cnt;
         a.b_events = n_events;
-        hipError_t sb = hough::launch_band(a, c.wg_threads / 64, c.band_lds, s);
+        hipError_t sb = hough::launch_band(a, f.wg_threads / 64, c.band_lds, s);
         if (sb != hipSuccess) return fail(&c, HOUGH_ERR_DEVICE, std::string("band launch failed: ") + hipGetErrorString(sb));
     }
-    if (longest_first && n_events > std::max(c.max_resident, kOrderMin)) {
+    if (longest_first && n_events > std::max(f.max_resident, kOrderMin)) {
         // the longest events start first and the short ones fill the CUs at
         // the end of the launch (with no more events than resident
         // workgroups every event starts at once and the order is moot)
@@ -556,7 +610,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
         (void)hipEventRecord(e0, s);
     }
     hipError_t st = c.cfg.peak_mode == 2 ? hough::launch_find_cf(a, c.wg_threads, c.lds_bytes, s)
-                                         : hough::launch_find(a, c.wg_threads, c.lds_bytes, s);
+                                         : hough::launch_find(a, f.wg_threads, f.lds_bytes, s);
     if (st != hipSuccess) return fail(&c, HOUGH_ERR_DEVICE, std::string("finder launch failed: ") + hipGetErrorString(st));
     if (e0) {
         (void)hipEventRecord(e1, s);

@@ -46,7 +46,17 @@ struct Workspace {
     int32_t big_pk = 0;        // peak entries per slot list
 };
 
-struct Ctx {
+// A launch shape of the finder and the LDS layout that goes with it.
+struct Shape {
+    int tile_rows = 0, wg_threads = 0, tile_bytes = 0, lds_bytes = 0;
+    int hs_cap = 0, stream_ok = 0, hs_off = 0, sorted_off = 0;
+    int big_sort = 0;                         // longest equal-count run sorted in LDS
+    int big_ok = 0, roll_off = 0, roll_bytes = 0;  // banded large-event sweep
+    int max_resident = 0;                     // finder workgroups resident at once on the device
+};
+
+// The context's own shape is the configuration's, or the default.
+struct Ctx : Shape {
     uint32_t magic = kCtxMagic;
     hough_config cfg{};
     int device = 0;
@@ -62,15 +72,12 @@ struct Ctx {
     float2 *d_ccs = nullptr;
     int c_theta = 0, c_rho = 0, f_theta = 0, f_rho = 0;
     // launch shape
-    int tile_rows = 0, wg_threads = 0, pitch = 0, tile_bytes = 0, lds_bytes = 0;
-    int sweep_groups = 0, sweep_threads = 256, hs_cap = 0;
+    int pitch = 0;
+    int sweep_groups = 0, sweep_threads = 256;
+    Shape dense;                              // two workgroups per CU, for calls of many events (max_resident 0: none)
     int single_split = 0;                     // calls of a few events split their first sweeps
     int band_split = 0, band_lds = 0;         // and their large events' first banded sweeps (k_band)
-    int stream_ok = 0, hs_off = 0, sorted_off = 0;
     int big_pk = 0;                           // peak entries per large-event slot
-    int big_sort = 0;                         // longest equal-count run sorted in LDS
-    int big_ok = 0, roll_off = 0, roll_bytes = 0;  // banded large-event sweep
-    int max_resident = 0;                     // finder workgroups resident at once on the device
     int tw_lds = 0;                           // LDS of the time-sliced finder's workgroups
     double safe_r2 = -1.0;
     int dump_rows = 0, dump_lds = 0;
@@ -113,8 +120,10 @@ void free_context(Ctx *c);
 hough_status ensure_workspace(const Ctx &c, Workspace &w, int64_t n_hits, int64_t n_events, hipStream_t s);
 // Bytes of a workspace for exactly nh hits and ne events whose large-event
 // slots hold big_pk peak entries per list; with base non-NULL, also points
-// w's arrays into base (the caller clears what must start at zero).
-size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, char *base, Workspace *w);
+// w's arrays into base (the caller clears what must start at zero). dense:
+// slots for as many workgroups as the dense shape has resident.
+size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, char *base, Workspace *w,
+                        bool dense = false);
 void free_workspace(Workspace &w);
 // Enqueues one finder call on s (split sweep, finder, compaction); outputs
 // as in hough_find. With longest_first, a call of many events runs its
@@ -123,9 +132,9 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
                           const int64_t *offsets, const float *z, const int16_t *vane, int32_t max_iters,
                           hough_candidate *cand, int32_t *hit_index, int64_t *counts, bool timed,
                           bool longest_first);
-// The finder's arguments of context c on workspace w, but for the call's events,
-// hits and outputs.
-FindArgs find_args(const Ctx &c, const Workspace &w);
+// The finder's arguments of context c and shape f on workspace w, but for the
+// call's events, hits and outputs.
+FindArgs find_args(const Ctx &c, const Shape &f, const Workspace &w);
 
 }  // namespace rt
 }  // namespace hough

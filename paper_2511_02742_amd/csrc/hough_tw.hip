@@ -300,7 +300,7 @@ hough_status hough_tw_find(hough_ctx *ctx, void *stream, const hough_tw_config *
     A.counts = counts;
     A.n_windows = n_windows;
     // the windows' events: timeline b's hits from offsets[b] on
-    FindArgs F = find_args(*c, c->ws);
+    FindArgs F = find_args(*c, *c, c->ws);
     F.n_events = (int32_t)B;
     F.n_total = N;
     F.total_is_bound = 1;

@@ -639,3 +639,36 @@ def test_argmax_peak_after_peak(gpu_available, kw):
     for z, v in evs[:4]:
         one = eventgen.Batch(r=np.zeros(len(z), np.float32), z=z, vane=v, offsets=np.array([0, len(z)], np.int64), events=[])
         check_batch(one, "argmax alone %s" % kw, peak_mode=0, **kw)
+
+
+@pytest.mark.parametrize("kw", [{}, {"peak_mode": 0}, {"n_theta": 180, "n_rho": 1000}, {"n_theta": 180, "n_rho": 1000, "peak_mode": 0},
+                                {"n_theta": 512, "n_rho": 1000, "assoc_window": 1, "nms_radius": 2}])
+@pytest.mark.parametrize("n_events,levels", [(767, (1, 20)), (768, (1, 20)), (1100, (0, 4, 60)), (3072, (1, 3, 100))])
+def test_calls_of_many_events_agree_over_shapes(gpu_available, kw, n_events, levels):
+    # the library's own choice of shape for a call of many events (two
+    # workgroups per CU from 768 events of few hits on, from 3072 on for
+    # any) against the same call on the one-per-CU shape: every byte, eager,
+    # on a second call with the events in reverse, and captured
+    import torch
+    from paper_2511_02742_amd.hough import HoughFinder
+    rng = np.random.default_rng(n_events)
+    pool = [eventgen.pileup_event(53_000 + i, n_tracks=int(levels[i % len(levels)])) for i in range(96)]
+    pick = rng.integers(0, len(pool), n_events)
+    own, one = finder(**kw), finder(wg_threads=1024, **kw)
+    dev = torch.device("cuda", 0)
+    for order in (pick, pick[::-1]):
+        b = eventgen.make_batch([pool[i] for i in order])
+        t = [torch.from_numpy(x).to(dev) for x in (b.z, b.vane, b.offsets)]
+        got, want = own.find(*t).to_host(), one.find(*t).to_host()
+        assert got[2]["status"] == want[2]["status"] == 0 and got[2]["candidates"] == want[2]["candidates"] > 0
+        assert got[0].tobytes() == want[0].tobytes() and np.array_equal(got[1], want[1])
+        assert got[2]["iters"] == want[2]["iters"]
+    graph = HoughFinder(0, **kw).capture(*t)
+    for _ in range(3):
+        graph.out.cand.zero_()
+        own.find(*t)
+        rep = graph.launch()
+        torch.cuda.synchronize()
+        r = rep.to_host()
+        assert r[0].tobytes() == want[0].tobytes() and np.array_equal(r[1], want[1])
+    graph.close()
