@@ -1314,6 +1314,186 @@ __device__ __forceinline__ void ring_test(const FindArgs &A, const uint32_t *lst
     }
 }
 
+// Two 16-bit fields at a time.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_sub_sat(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t,
+                              __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
+// Whether band_scan can run: a row of at most 1024 words, held four 16-byte
+// units per lane, and counts that 16 bits and the test's bias hold.
+__device__ __forceinline__ bool band_scan_ok(const FindArgs &A, int n_alive) {
+    return A.peak_mode == 1 && A.nms_radius == 1 && A.pitch <= 16 * kWave && n_alive < 0x8000 &&
+           A.min_votes - 1u < 0x7fffu;
+}
+
+// Banded sweep of a large event for the 3 x 3 window, rows [r0, r1) of one wave
+// (and one row on either side), two rows at a time. Row j counts in the low
+// and row j + 1 in the high halves of the words of the wave's row buffer (word
+// `row_w`), by atomics that return nothing; the buffer is then read into
+// registers (lane l holds bins 256 u + 4 l + q) and cleared. With the pair
+// before (rows j - 2 and j - 1) that is enough to test rows j - 1 and j: their
+// counts are the high halves of the one and the low halves of the other, and
+// the rows above and below them are the two pairs as they are. The test is 16-bit
+// arithmetic on both rows at once, for the units (256 bins) that hold a bin
+// >= T; a neighbour with a lower flat index (row above, or left) wins ties.
+// The peaks go to seg[0, segcap) in flat-index order; returns their number.
+//
+// Bound by VALU issue, where the sweep that lists each row's bins >= T as the
+// votes lift them (band_ring) waited on a chain of LDS round trips per row: a
+// pileup-100 event has such bins in 6 of 7 rows. Measured: 256 pileup-100
+// events in a call 658 -> 510 us, a pileup-150 event alone 291 -> 237 us.
+// Hits: register chunks c < h.nch (REGS) at positions 64 c + lane, and nx LDS
+// chunks at positions x_base + 64 x + lane, below n_alive.
+template <bool REGS>
+__device__ __forceinline__ int band_scan(const FindArgs &A, const float2 *__restrict__ cs, uint32_t row_w,
+                                         const HitRegs &h, const float2 *xh, int x_base, int nx, int n_alive, int r0,
+                                         int r1, unsigned long long *seg, int segcap) {
+    const int lane = lane_id();
+    const uint32_t bias = 0x00010001u * (0x8000u - A.min_votes);
+    const int units = A.pitch / 4;
+    uint4 *const r4 = reinterpret_cast<uint4 *>(g_lds + row_w);
+    for (int x = lane; x < units; x += kWave) r4[x] = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t *const row = reinterpret_cast<uint32_t *>(g_lds) + row_w;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int nseg = 0;
+    float2 mine = make_float2(0.0f, 0.0f);
+    uint32_t q[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) q[i] = 0u;
+    for (int i = 0; r0 - 1 + i <= r1; i += 2) {
+        const int j = r0 - 1 + i;   // rows j and j + 1
+        if ((i & (kWave - 1)) == 0) {
+            // a row past the grid's edge adds nothing to the bins of the edge row
+            mine = cs[min(max(j + lane, 0), A.n_theta - 1)];
+        }
+        const uint32_t one_lo = j >= 0 && j < A.n_theta ? 1u : 0u;
+        const uint32_t one_hi = j + 1 < A.n_theta && j + 1 <= r1 ? 0x10000u : 0u;
+        float2 a, b;
+        a.x = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine.x), i & (kWave - 1)));
+        a.y = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine.y), i & (kWave - 1)));
+        b.x = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine.x), (i & (kWave - 1)) + 1));
+        b.y = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine.y), (i & (kWave - 1)) + 1));
+        auto vote = [&](float phi, float z) {
+            const int ka = rho_bin(phi, z, a.x, a.y, A.rho_min, A.inv_w);
+            const int kb = rho_bin(phi, z, b.x, b.y, A.rho_min, A.inv_w);
+            __hip_atomic_fetch_add(row + ka, one_lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            __hip_atomic_fetch_add(row + kb, one_hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        };
+        if constexpr (REGS) {
+#pragma unroll
+            for (int c = 0; c < kChunks; ++c)
+                if (c * kWave + lane < n_alive) vote(h.phi[c], h.z[c]);
+        }
+        for (int x = 0; x < nx; ++x)
+            if (x_base + x * kWave + lane < n_alive) {
+                const float2 pz = xh[x * kWave + lane];
+                vote(pz.x, pz.y);
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint32_t p[16];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int x = u * kWave + lane;
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (x < units) {
+                v = r4[x];
+                r4[x] = make_uint4(0u, 0u, 0u, 0u);
+            }
+            p[4 * u] = v.x;
+            p[4 * u + 1] = v.y;
+            p[4 * u + 2] = v.z;
+            p[4 * u + 3] = v.w;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // rows j - 1 (low halves) and j: the bins >= T of the wave's own rows
+        const bool lo_own = j - 1 >= r0 && j - 1 < r1, hi_own = j >= r0 && j < r1;
+        const uint32_t own = (lo_own ? 0x8000u : 0u) | (hi_own ? 0x80000000u : 0u);
+        const uint32_t thr = (lo_own ? A.min_votes - 1u : 0xffffu) | (hi_own ? (A.min_votes - 1u) << 16 : 0xffff0000u);
+        uint32_t found = 0u;   // bit 4 u + q: row j - 1's bin is a peak; 16 above: row j's
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            uint32_t c[6], f = 0u;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                c[t + 1] = __builtin_amdgcn_alignbit(p[4 * u + t], q[4 * u + t], 16);
+                f |= c[t + 1] + bias;
+            }
+            if (__ballot((f & own) != 0u) == 0ull) continue;
+            // the bins beside the lane's four: its neighbours', or the next unit's
+            uint32_t pw[6], qw[6];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                pw[t + 1] = p[4 * u + t];
+                qw[t + 1] = q[4 * u + t];
+            }
+            auto left = [&](const uint32_t *w) {   // word 3 of the lane below
+                const int first = u > 0 ? __builtin_amdgcn_readlane((int)w[4 * u - 1], kWave - 1) : 0;
+                return (uint32_t)__builtin_amdgcn_update_dpp(first, (int)w[4 * u + 3], 0x138, 0xf, 0xf, false);
+            };
+            auto right = [&](const uint32_t *w) {  // word 0 of the lane above
+                const int end = u < 3 ? __builtin_amdgcn_readlane((int)w[(4 * u + 4) & 15], 0) : 0;
+                return (uint32_t)__builtin_amdgcn_update_dpp(end, (int)w[4 * u], 0x130, 0xf, 0xf, false);
+            };
+            pw[0] = left(p);
+            pw[5] = right(p);
+            qw[0] = left(q);
+            qw[5] = right(q);
+            c[0] = __builtin_amdgcn_alignbit(pw[0], qw[0], 16);
+            c[5] = __builtin_amdgcn_alignbit(pw[5], qw[5], 16);
+#pragma unroll
+            for (int t = 1; t < 5; ++t) {
+                const uint32_t above = pk_max(pk_max(qw[t - 1], qw[t]), qw[t + 1]);
+                const uint32_t below = pk_max(pk_max(pw[t - 1], pw[t]), pw[t + 1]);
+                // greater than these, and not below those
+                const uint32_t x = pk_max(pk_max(above, c[t - 1]), thr);
+                const uint32_t y = pk_sub_sat(pk_max(below, c[t + 1]), 0x00010001u);
+                found |= pk_min(pk_sub_sat(c[t], pk_max(x, y)), 0x00010001u) << (4 * u + t - 1);
+            }
+        }
+        if (__ballot(found != 0u) != 0ull) {
+#pragma unroll
+            for (int row = 0; row < 2; ++row) {
+                const uint32_t mine_row = (found >> (16 * row)) & 0xffffu;
+                if (__ballot(mine_row != 0u) == 0ull) continue;
+                const uint32_t flat = (uint32_t)((j - 1 + row) * A.n_rho);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t nib = (mine_row >> (4 * u)) & 15u;
+                    if (__ballot(nib != 0u) == 0ull) continue;
+                    int at = nseg, total = 0;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const unsigned long long m = __ballot(((nib >> t) & 1u) != 0u);
+                        at += mbcnt64(m);
+                        total += __popcll(m);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        if ((nib >> t) & 1u) {
+                            const uint32_t cnt = __builtin_amdgcn_alignbit(p[4 * u + t], q[4 * u + t], 16) >> (16 * row);
+                            if (at < segcap)
+                                seg[at] = bin_key(cnt & 0xffffu, flat + (uint32_t)(4 * (u * kWave + lane) + t));
+                            ++at;
+                        }
+                    }
+                    nseg += total;
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) q[t] = p[t];
+    }
+    return nseg;
+}
+
 // Banded row-stream sweep of a large event for a 3 x 3 window with 16-bit
 // counts (two bins per LDS word; an event on this path has fewer than 2^16
 // alive hits, so a count never carries into its neighbour). Wave w streams
@@ -1364,6 +1544,15 @@ __device__ __forceinline__ void band_ring(const FindArgs &A, const float2 *__res
     }
     if (r0 >= r1) return;
     int nseg = 0;
+    if (band_scan_ok(A, n_alive)) {
+        nseg = band_scan<true>(A, cs, ring0, h, xh, kChunks * kWave, nx, n_alive, r0, r1,
+                               pk + (size_t)wave * (A.big_pk / NW), A.big_pk / NW);
+        if (lane == 0) {
+            rc[3] = nseg;
+            rc[4] = nseg > A.big_pk / NW ? 1 : 0;
+        }
+        return;
+    }
     const int jlo = max(r0 - 1, 0);
     const int jhi = min(r1 + 1, A.n_theta);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -3065,12 +3254,16 @@ __global__ __launch_bounds__(NTB) void k_band(FindArgs A, const float2 *__restri
     int *rc = s_rc[wave];
     int nseg = 0;
     bool ovf = false;
-    {
+    const bool scan = band_scan_ok(A, n);
+    if (scan) {
+        if (r0 < r1)
+            nseg = band_scan<false>(A, cs, rings + (uint32_t)(wave * A.pitch), HitRegs{}, xy, 0, nx, n, r0, r1, pk, kSegW);
+    } else {
         uint2 *q = reinterpret_cast<uint2 *>(g_lds + ring0);
         for (int x = lane; x < 3 * hw / 2; x += kWave) q[x] = make_uint2(0u, 0u);
         if (lane < 3) rc[lane] = 0;
     }
-    if (r0 < r1) {
+    if (r0 < r1 && !scan) {
         const int jlo = max(r0 - 1, 0);
         const int jhi = min(r1 + 1, A.n_theta);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -672,3 +672,34 @@ def test_calls_of_many_events_agree_over_shapes(gpu_available, kw, n_events, lev
         r = rep.to_host()
         assert r[0].tobytes() == want[0].tobytes() and np.array_equal(r[1], want[1])
     graph.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho", [(9000, 1000), (1000, 1024), (1001, 1025), (333, 768), (255, 257), (64, 256), (33, 1021),
+                                           (17, 4), (15, 252), (2, 1000), (1, 1000), (400, 513)])
+@pytest.mark.parametrize("min_votes", [3, 6, 40])
+def test_large_event_rows_by_pairs(gpu_available, n_theta, n_rho, min_votes):
+    # large events on grids at the edges of the banded sweep's units: rows of
+    # up to 1024 bins are tested 256 bins at a time, two rows together (one
+    # more bin, 1025, takes the sweep by listed bins); bands of one row, of
+    # none, and of an odd number of rows. Many z values repeat, so neighbours
+    # tie, in a row, across rows and across the units' edges
+    rng = np.random.default_rng(n_theta * 1000 + n_rho)
+    evs = [eventgen.pileup_event(54_000 + i, n_tracks=n) for i, n in enumerate((100, 115))]
+    z = np.concatenate([ev.z for ev in evs])
+    rep = rng.random(len(z)) < 0.3
+    z[rep] = (np.round(z[rep] / 8.0) * 8.0).astype(np.float32)
+    off = np.concatenate([[0], np.cumsum([ev.n_hits for ev in evs])]).astype(np.int64)
+    assert min(np.diff(off)) > 512
+    b = eventgen.Batch(r=np.zeros(off[-1], np.float32), z=z, vane=np.concatenate([ev.vane for ev in evs]), offsets=off, events=[])
+    kw = dict(n_theta=n_theta, n_rho=n_rho, min_votes=min_votes, max_iters=3)
+    _, want = check_batch(b, "rows by pairs alone %s" % kw, **kw)   # k_band's first sweep
+    # and among many events, where the finder takes every sweep
+    many = eventgen.Batch(r=np.zeros(260 * off[-1], np.float32), z=np.tile(b.z, 260), vane=np.tile(b.vane, 260),
+                          offsets=np.concatenate([off[:-1] + i * off[-1] for i in range(260)] + [[260 * off[-1]]]).astype(np.int64), events=[])
+    got = run_batch(finder(**kw), many)
+    n, m = len(want.cand), len(want.hit_index)
+    assert got[2]["status"] == 0 and len(got[0]) == 260 * n and np.array_equal(got[1].reshape(260, m), np.tile(want.hit_index, (260, 1)))
+    cand = got[0].reshape(260, n)
+    for f in FIELDS:
+        base = {"event": 2, "hit_offset": m}.get(f, 0) * np.arange(260)[:, None]
+        assert np.array_equal(cand[f] - base.astype(cand[f].dtype), np.tile(want.cand[f], (260, 1))), (kw, f)
