@@ -978,15 +978,12 @@ __device__ __forceinline__ bool recount_by_lanes(int n_hs, int n_alive, int nch)
 // in the slot; the peaks are sorted in the row buffers.
 // ---------------------------------------------------------------------------
 
-// Workgroup barrier that also orders the workgroup's device-memory writes
-// before its later reads (the slot arrays are written and read by different
-// waves; the acquire drops L1 lines an earlier event left behind).
-__device__ __forceinline__ void sync_global() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-}
-
+// A large event's slot arrays are written and read by the waves of one
+// workgroup, through the CU's own L1: a barrier orders them. Only a slot's way
+// from one workgroup to the next (another XCD's L2) takes an agent fence, by
+// the one thread that takes or returns the flag, after or before a barrier.
+// An agent fence in every wave at every exchange (a write-back of the whole L2
+// each) took 43 % of a pileup-100 event's time among 256 (405 -> 227 us).
 struct Slot {
     unsigned long long *pk;   // peak keys in the order found, big_pk
     unsigned long long *srt;  // the same keys ordered, big_pk
@@ -1012,16 +1009,19 @@ __device__ __forceinline__ int acquire_slot(const FindArgs &A, Shared &sh) {
             if (atomicCAS(&A.pool_flags[c], 0, 1) == 0) got = c;
         }
         sh.slot = got;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-    sync_global();
+    __syncthreads();
     return sh.slot;
 }
 
 __device__ __forceinline__ void release_slot(const FindArgs &A, int s) {
     if (s < 0) return;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
-    if (tid_x() == 0) atomicExch(&A.pool_flags[s], 0);
+    if (tid_x() == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        atomicExch(&A.pool_flags[s], 0);
+    }
 }
 
 // Loads the first 512 alive hits into registers and the rest into LDS at xh;
@@ -1655,7 +1655,7 @@ __device__ __forceinline__ int order_peaks(const FindArgs &A, const Lds &L, cons
     const int lane = lane_id();
     if (npk <= 1) {
         if (npk == 1 && tid_x() == 0) S.srt[0] = S.pk[0];
-        sync_global();
+        __syncthreads();
         return npk;
     }
     const int cmax = sh.nalive;                    // a count never exceeds the alive hits
@@ -1696,7 +1696,7 @@ __device__ __forceinline__ int order_peaks(const FindArgs &A, const Lds &L, cons
         const unsigned long long key = S.pk[i];
         S.srt[atomicAdd(&cur[(uint32_t)(key >> 32)], 1)] = key;
     }
-    sync_global();
+    __syncthreads();
     unsigned long long *buf = reinterpret_cast<unsigned long long *>(L.tile);
     for (int r = 0; r < nruns; ++r) {
         const int st = (int)runs[2 * r];
@@ -1709,7 +1709,7 @@ __device__ __forceinline__ int order_peaks(const FindArgs &A, const Lds &L, cons
         for (int i = tid_x(); i < len; i += NT) S.srt[st + i] = buf[i];
         __syncthreads();
     }
-    sync_global();
+    __syncthreads();
     return npk;
 }
 
@@ -1802,7 +1802,7 @@ __device__ __forceinline__ int order_segments(const FindArgs &A, const Lds &L, c
             }
         }
     }
-    sync_global();
+    __syncthreads();
     return ovf || wide ? -1 : npk;
 }
 
@@ -2963,7 +2963,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                     } else {
                         band_big<NT>(A, cs, L, h, xh, nx, n_alive, S.pk, sh);
                     }
-                    sync_global();
+                    __syncthreads();
                     HOUGH_PHASE_MARK(kPhBigSweep);
                     evals += (unsigned long long)n_alive * (unsigned long long)A.n_theta;
                     votes += (unsigned long long)n_alive * (unsigned long long)A.n_theta;
@@ -2972,7 +2972,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                         if (MAX) {
                             const unsigned long long best = sh.best;
                             if (tid_x() == 0) S.srt[0] = best;
-                            sync_global();
+                            __syncthreads();
                             npk = best != 0ull ? 1 : 0;
                         } else if (ring) {
                             npk = order_segments<NT>(A, L, S, sh);
