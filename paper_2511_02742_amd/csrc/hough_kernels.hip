@@ -61,6 +61,13 @@ __device__ __forceinline__ uint32_t lds_byte(uint32_t w) {
 constexpr int kChunks = 8;  // register-resident hit chunks per wave (512 hits)
 constexpr int kMaxLists = 5;  // row lists of the banded sweep: 2 w + 1 for w <= 2
 constexpr int kClaimBlockW = 8;  // alive-hit words up to which claims are resolved in registers
+// Alive hits above which an event's first sweep is banded (band_scan) even
+// though its hits fit the registers: the row-by-row sweep's cost goes with the
+// hits, and its hot set often outgrows LDS there, so that it was done for
+// nothing. With the line at no hits / 384 / 320 / 256: 256 pileup-70 events 346 /
+// 242 / 243 / 243 us, 512 pileup-60 events at two per CU 454 / 350 / 297 / 299,
+// 1024 pileup-50 events 408 / 395 / 400 / 449.
+constexpr int kBandHits = 352;
 constexpr int kSegCounts = 128;  // vote counts T .. T + 127 ordered by order_segments
 
 __device__ __forceinline__ int wave_id() {
@@ -2782,6 +2789,10 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
     bool first = true;
     int n_hs = 0;          // entries of the hot set
     bool hs_valid = false; // the hot set holds every bin >= T of the current histogram
+    // alive hits above which the first iteration's sweep is banded
+    int band_from = A.g_hs == nullptr && A.big_ok != 0 && band_scan_ok(A, kBandHits) && band_ring_ok<NT>(A, kBandHits, 0)
+                        ? kBandHits
+                        : kChunks * kWave;
     bool big = false;      // large-event path this iteration: peaks in a device-memory slot
     bool big_lds = false;  // the hot set or the peak list outgrew LDS: the event stays large
     int slot = -1;
@@ -2844,8 +2855,10 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
         // the large-event path; once fewer hits are left the next one sweeps
         // row by row again (a fresh histogram either way), unless the hot set
         // or the peak list outgrew LDS in an earlier iteration
-        // (and the first iteration of an event whose first band k_band swept)
-        big = big_lds || nbatch > 1 || (iter == 0 && sh.pre == NW);
+        // (and the first iteration of an event whose first band k_band swept,
+        // or of many hits)
+        const bool by_band = !MAX && iter == 0 && n_alive > band_from && n_alive <= kChunks * kWave;
+        big = big_lds || nbatch > 1 || (iter == 0 && sh.pre == NW) || by_band;
         // (the LDS-resident hits are read in whole 64-hit chunks, at most
         // 56 of them: the banded sweep flags hot votes in 64 bits)
         if (A.stream_ok && n_alive <= kChunks * kWave + min(A.hs_cap & ~(kWave - 1), 56 * kWave)) {
@@ -2998,6 +3011,12 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                         ++hs_full;
                     }
                 }
+            }
+            if (by_band && !done) {
+                // no slot, hits that leave the grid, or more peaks in a band
+                // than its segment holds: as an event of fewer hits
+                band_from = kChunks * kWave;
+                continue;
             }
         }
         if (!done) {

@@ -694,12 +694,42 @@ def test_large_event_rows_by_pairs(gpu_available, n_theta, n_rho, min_votes):
     kw = dict(n_theta=n_theta, n_rho=n_rho, min_votes=min_votes, max_iters=3)
     _, want = check_batch(b, "rows by pairs alone %s" % kw, **kw)   # k_band's first sweep
     # and among many events, where the finder takes every sweep
-    many = eventgen.Batch(r=np.zeros(260 * off[-1], np.float32), z=np.tile(b.z, 260), vane=np.tile(b.vane, 260),
-                          offsets=np.concatenate([off[:-1] + i * off[-1] for i in range(260)] + [[260 * off[-1]]]).astype(np.int64), events=[])
+    check_repeated(b, want, 260, kw)
+
+
+def check_repeated(b, want, times, kw):
+    """The batch b repeated `times` times in one call, against its oracle result."""
+    n, m, ne = len(want.cand), len(want.hit_index), len(b.offsets) - 1
+    off = np.concatenate([b.offsets[:-1] + i * b.offsets[-1] for i in range(times)] + [[times * b.offsets[-1]]]).astype(np.int64)
+    many = eventgen.Batch(r=np.zeros(off[-1], np.float32), z=np.tile(b.z, times), vane=np.tile(b.vane, times), offsets=off, events=[])
     got = run_batch(finder(**kw), many)
-    n, m = len(want.cand), len(want.hit_index)
-    assert got[2]["status"] == 0 and len(got[0]) == 260 * n and np.array_equal(got[1].reshape(260, m), np.tile(want.hit_index, (260, 1)))
-    cand = got[0].reshape(260, n)
+    assert got[2]["status"] == 0 and len(got[0]) == times * n and len(got[1]) == times * m, (kw, got[2])
+    assert np.array_equal(got[1].reshape(times, m), np.tile(want.hit_index, (times, 1))), kw
+    cand = got[0].reshape(times, n)
     for f in FIELDS:
-        base = {"event": 2, "hit_offset": m}.get(f, 0) * np.arange(260)[:, None]
-        assert np.array_equal(cand[f] - base.astype(cand[f].dtype), np.tile(want.cand[f], (260, 1))), (kw, f)
+        base = ({"event": ne, "hit_offset": m}.get(f, 0) * np.arange(times)[:, None]).astype(cand[f].dtype)
+        assert np.array_equal(cand[f] - base, np.tile(want.cand[f], (times, 1))), (kw, f)
+    return got
+
+
+@pytest.mark.parametrize("kw", [{}, {"wg_threads": 512, "tile_rows": 14}, {"wg_threads": 256, "tile_rows": 6}, {"min_votes": 3},
+                                {"n_theta": 9000, "n_rho": 1000, "min_votes": 3}, {"n_theta": 180, "n_rho": 1000},
+                                {"n_rho": 1100}, {"nms_radius": 2}, {"peak_mode": 0, "max_iters": 9},
+                                {"rho_min": -300.0, "rho_max": 300.0, "max_iters": 2}])
+def test_first_sweep_by_band(gpu_available, kw):
+    # events around the size from which the first sweep is banded though the
+    # hits fit the registers (more than 352), to 512 and past it, in a call of
+    # many events; 9000 rows at T = 3 overflow a band's peak segment, and a
+    # narrow rho range holds hits that leave the grid: both sweep as an event
+    # of fewer hits does
+    evs = []
+    for i, n in enumerate((352, 353, 384, 447, 449, 512, 513)):
+        ev = eventgen.pileup_event(55_000 + i, n_tracks=n // 3 + 12)
+        assert ev.n_hits >= n
+        evs.append((ev.z[:n], ev.vane[:n]))
+    off = np.concatenate([[0], np.cumsum([len(z) for z, _ in evs])]).astype(np.int64)
+    b = eventgen.Batch(r=np.zeros(off[-1], np.float32), z=np.concatenate([z for z, _ in evs]),
+                       vane=np.concatenate([v for _, v in evs]), offsets=off, events=[])
+    f = finder(**kw)
+    want = oracle_find_batch(_ocfg(f.config), b.offsets, b.z, b.vane)
+    check_repeated(b, want, 40, kw)
