@@ -1334,10 +1334,12 @@ __device__ __forceinline__ uint32_t pk_sub_sat(uint32_t a, uint32_t b) {
                               __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 
-// Whether band_scan can run: a row of at most 1024 words, held four 16-byte
-// units per lane, and counts that 16 bits and the test's bias hold.
+// Whether band_scan can run: the largest bin or a 3 x 3 window, a row of at most
+// 1024 words, held four 16-byte units per lane, and counts that 16 bits and the
+// test's bias hold.
+template <bool MAX>
 __device__ __forceinline__ bool band_scan_ok(const FindArgs &A, int n_alive) {
-    return A.peak_mode == 1 && A.nms_radius == 1 && A.pitch <= 16 * kWave && n_alive < 0x8000 &&
+    return (MAX || (A.peak_mode == 1 && A.nms_radius == 1)) && A.pitch <= 16 * kWave && n_alive < 0x8000 &&
            A.min_votes - 1u < 0x7fffu;
 }
 
@@ -1359,8 +1361,14 @@ __device__ __forceinline__ bool band_scan_ok(const FindArgs &A, int n_alive) {
 // events in a call 658 -> 510 us, a pileup-150 event alone 291 -> 237 us.
 // Hits: register chunks c < h.nch (REGS) at positions 64 c + lane, and nx LDS
 // chunks at positions x_base + 64 x + lane, below n_alive.
-template <bool REGS>
-__device__ __forceinline__ int band_scan(const FindArgs &A, const float2 *__restrict__ cs, uint32_t row_w,
+//
+// MAX: the band's largest key of the bins >= T instead (0: none), over rows
+// [r0, r1) alone. Only a count above the largest so far is looked at for its
+// place (an equal one of a later row loses), so a pair of rows costs its votes
+// and 16 packed maxima. 1024 argmax events of 100 tracks on 180 x 1000 bins
+// 1609 -> 1005 us, 1 % of 200 tracks among 1024 of 10 6338 -> 2308 us.
+template <bool REGS, bool MAX>
+__device__ __forceinline__ unsigned long long band_scan(const FindArgs &A, const float2 *__restrict__ cs, uint32_t row_w,
                                          const HitRegs &h, const float2 *xh, int x_base, int nx, int n_alive, int r0,
                                          int r1, unsigned long long *seg, int segcap) {
     const int lane = lane_id();
@@ -1371,18 +1379,21 @@ __device__ __forceinline__ int band_scan(const FindArgs &A, const float2 *__rest
     uint32_t *const row = reinterpret_cast<uint32_t *>(g_lds) + row_w;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     int nseg = 0;
+    unsigned long long best = 0ull;
+    uint32_t top = A.min_votes - 1u;   // MAX: a bin has to exceed it
     float2 mine = make_float2(0.0f, 0.0f);
     uint32_t q[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) q[i] = 0u;
-    for (int i = 0; r0 - 1 + i <= r1; i += 2) {
-        const int j = r0 - 1 + i;   // rows j and j + 1
+    const int j_lo = MAX ? r0 : r0 - 1, j_hi = MAX ? r1 - 1 : r1;   // first and last row voted
+    for (int i = 0; j_lo + i <= j_hi; i += 2) {
+        const int j = j_lo + i;   // rows j and j + 1
         if ((i & (kWave - 1)) == 0) {
             // a row past the grid's edge adds nothing to the bins of the edge row
             mine = cs[min(max(j + lane, 0), A.n_theta - 1)];
         }
         const uint32_t one_lo = j >= 0 && j < A.n_theta ? 1u : 0u;
-        const uint32_t one_hi = j + 1 < A.n_theta && j + 1 <= r1 ? 0x10000u : 0u;
+        const uint32_t one_hi = j + 1 < A.n_theta && j + 1 <= j_hi ? 0x10000u : 0u;
         float2 a, b;
         a.x = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine.x), i & (kWave - 1)));
         a.y = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine.y), i & (kWave - 1)));
@@ -1420,6 +1431,24 @@ __device__ __forceinline__ int band_scan(const FindArgs &A, const float2 *__rest
             p[4 * u + 3] = v.w;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if constexpr (MAX) {
+            uint32_t m = p[0];
+#pragma unroll
+            for (int t = 1; t < 16; ++t) m = pk_max(m, p[t]);
+            if (__ballot((m & 0xffffu) > top || (m >> 16) > top) == 0ull) continue;
+            unsigned long long key = best;
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                const uint32_t flat = (uint32_t)(j * A.n_rho + 4 * ((t >> 2) * kWave + lane) + (t & 3));
+                const uint32_t lo = p[t] & 0xffffu, hi = p[t] >> 16;
+                const unsigned long long ka = bin_key(lo, flat), kb = bin_key(hi, flat + (uint32_t)A.n_rho);
+                key = lo > top && ka > key ? ka : key;
+                key = hi > top && kb > key ? kb : key;
+            }
+            best = wave_max64(key);
+            top = (uint32_t)(best >> 32);
+            continue;
+        }
         // rows j - 1 (low halves) and j: the bins >= T of the wave's own rows
         const bool lo_own = j - 1 >= r0 && j - 1 < r1, hi_own = j >= r0 && j < r1;
         const uint32_t own = (lo_own ? 0x8000u : 0u) | (hi_own ? 0x80000000u : 0u);
@@ -1498,7 +1527,8 @@ __device__ __forceinline__ int band_scan(const FindArgs &A, const float2 *__rest
 #pragma unroll
         for (int t = 0; t < 16; ++t) q[t] = p[t];
     }
-    return nseg;
+    if constexpr (MAX) return best;
+    return (unsigned long long)nseg;
 }
 
 // Banded row-stream sweep of a large event for a 3 x 3 window with 16-bit
@@ -1513,7 +1543,7 @@ __device__ __forceinline__ int band_scan(const FindArgs &A, const float2 *__rest
 // writes its peaks to its own segment pk[w * big_pk / NW ...] in flat-index
 // order and leaves their number in rc[3] (rc[4] set: the segment overflowed);
 // argmax mode takes the largest key of the listed bins instead.
-template <int NT>
+template <int NT, bool MAX>
 __device__ __forceinline__ void band_ring(const FindArgs &A, const float2 *__restrict__ cs, const Lds &L,
                                           const HitRegs &h, const float2 *xh, int nx, int n_alive,
                                           unsigned long long *pk, Shared &sh) {
@@ -1551,9 +1581,15 @@ __device__ __forceinline__ void band_ring(const FindArgs &A, const float2 *__res
     }
     if (r0 >= r1) return;
     int nseg = 0;
-    if (band_scan_ok(A, n_alive)) {
-        nseg = band_scan<true>(A, cs, ring0, h, xh, kChunks * kWave, nx, n_alive, r0, r1,
-                               pk + (size_t)wave * (A.big_pk / NW), A.big_pk / NW);
+    if (band_scan_ok<MAX>(A, n_alive)) {
+        const unsigned long long got =
+            band_scan<true, MAX>(A, cs, ring0, h, xh, kChunks * kWave, nx, n_alive, r0, r1,
+                                 pk + (size_t)wave * (A.big_pk / NW), A.big_pk / NW);
+        if (MAX) {
+            if (lane == 0 && got != 0ull) atomicMax(&sh.best, got);
+            return;
+        }
+        nseg = (int)got;
         if (lane == 0) {
             rc[3] = nseg;
             rc[4] = nseg > A.big_pk / NW ? 1 : 0;
@@ -2790,7 +2826,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
     int n_hs = 0;          // entries of the hot set
     bool hs_valid = false; // the hot set holds every bin >= T of the current histogram
     // alive hits above which the first iteration's sweep is banded
-    int band_from = A.g_hs == nullptr && A.big_ok != 0 && band_scan_ok(A, kBandHits) && band_ring_ok<NT>(A, kBandHits, 0)
+    int band_from = A.g_hs == nullptr && A.big_ok != 0 && band_scan_ok<false>(A, kBandHits) && band_ring_ok<NT>(A, kBandHits, 0)
                         ? kBandHits
                         : kChunks * kWave;
     bool big = false;      // large-event path this iteration: peaks in a device-memory slot
@@ -2972,7 +3008,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                         // k_band swept this band into the slot (the segment
                         // counts were taken over at the start)
                     } else if (ring) {
-                        band_ring<NT>(A, cs, L, h, xh, nx, n_alive, S.pk, sh);
+                        band_ring<NT, MAX>(A, cs, L, h, xh, nx, n_alive, S.pk, sh);
                     } else {
                         band_big<NT>(A, cs, L, h, xh, nx, n_alive, S.pk, sh);
                     }
@@ -3273,10 +3309,11 @@ __global__ __launch_bounds__(NTB) void k_band(FindArgs A, const float2 *__restri
     int *rc = s_rc[wave];
     int nseg = 0;
     bool ovf = false;
-    const bool scan = band_scan_ok(A, n);
+    const bool scan = band_scan_ok<false>(A, n);
     if (scan) {
         if (r0 < r1)
-            nseg = band_scan<false>(A, cs, rings + (uint32_t)(wave * A.pitch), HitRegs{}, xy, 0, nx, n, r0, r1, pk, kSegW);
+            nseg = (int)band_scan<false, false>(A, cs, rings + (uint32_t)(wave * A.pitch), HitRegs{}, xy, 0, nx, n, r0, r1,
+                                                pk, kSegW);
     } else {
         uint2 *q = reinterpret_cast<uint2 *>(g_lds + ring0);
         for (int x = lane; x < 3 * hw / 2; x += kWave) q[x] = make_uint2(0u, 0u);

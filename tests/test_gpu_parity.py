@@ -733,3 +733,19 @@ def test_first_sweep_by_band(gpu_available, kw):
     f = finder(**kw)
     want = oracle_find_batch(_ocfg(f.config), b.offsets, b.z, b.vane)
     check_repeated(b, want, 40, kw)
+
+
+@pytest.mark.parametrize("kw", [{}, {"wg_threads": 512, "tile_rows": 14}, {"n_rho": 1025}, {"n_theta": 33, "n_rho": 257},
+                                {"n_theta": 1, "n_rho": 64}, {"n_theta": 9000, "n_rho": 1000, "min_votes": 40}, {"min_votes": 200}])
+def test_large_argmax_rows_by_pairs(gpu_available, kw):
+    # the largest bin of a large event by the banded sweep of two rows at a
+    # time: rows of a whole number of units and one bin more, bands of one row,
+    # of none and of an odd number, many equal bins (lowest flat index wins)
+    evs = [eventgen.pileup_event(56_000 + i, n_tracks=n) for i, n in enumerate((100, 130, 90))]
+    b = eventgen.make_batch(evs)
+    assert (np.diff(b.offsets) > 512).sum() >= 2
+    z = (np.round(b.z / 4.0) * 4.0).astype(np.float32)
+    b = eventgen.Batch(r=b.r, z=z, vane=b.vane, offsets=b.offsets, events=[])
+    kw = dict(peak_mode=0, max_iters=6, **kw)
+    _, want = check_batch(b, "large argmax %s" % kw, **kw)
+    check_repeated(b, want, 90, kw)
