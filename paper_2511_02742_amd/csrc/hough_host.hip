@@ -78,20 +78,29 @@ constexpr int kSmallCall = 8;
 // so that one event's chains of dependent steps overlap the other's sweep. An
 // event takes longer in it, and its shorter lists send more events to the
 // large-event path, whose length ends the call: it pays once the events outnumber
-// the workgroups. Against the default shape, ratio of times (1024 x 1024 bins):
-//   27 hits per event     1.18 at 512 events, 1.36 at 1024, 1.46 at 4096
-//   110 hits (Poisson)    0.80 at 384, 1.3 at 768, 1.48 at 4096
-//   275 hits              0.75 at 1024, 1.0 at 2048, 1.33 at 3072
-//   550 hits              1.06 at 768, 1.4 at 3072
-//   1 to 100 tracks mixed 0.83 at 1024, 1.2 at 2048 and 3072, 1.39 at 4096
-// and on 180 rows, where few bins reach T, with 275 hits 1.38 (every local
-// maximum) and 1.5 (largest bin) at 768 events. With fewer than kDenseRho rho
-// bins more bins reach T than its hot set holds (512 x 512 bins, 110 hits: 0.5 at
-// 768 events, 0.9 at 2048).
+// the workgroups. Local maxima, default shape's time / this one's (us):
+//   1024 x 1024 bins   512 events     768          1024         4096
+//   27 hits            82 / 67        108 / 89     136 / 99     449 / 303
+//   110 hits           132 / 102      166 / 127    211 / 149    721 / 473
+//   275 hits           245 / 266      319 / 266    398 / 307    1458 / 1031
+//   550 hits           555 / 531      800 / 714    1053 / 917   3870 / 3202
+//   1 to 150 tracks                   570 / 575    727 / 632    2848 / 2234
+// and alike on 180 rows (550 hits at 1024 events 638 / 474). Below kDenseRho rho
+// bins more bins reach T than its hot set holds (512 x 512 bins, 139 hits:
+// 216 / 236 at 1024 events, 726 / 469 at 4096), and so on more than kDenseRows rows
+// (9000, 56 hits: 939 / 1409 at 1024). The largest bin alone goes peak after peak on
+// the hot set, and one that does not fit costs a sweep per peak: only events
+// of few hits and votes take the shape (1024 events of 275 hits on 180 rows
+// 237 / 146, on 1024 rows 450 / 2401).
+// The host knows the events' number and mean size, not the largest: a few events
+// that dwarf the rest end their call later in it (1 % of 200 tracks among 768 of 10
+// on 180 rows 492 / 629).
 constexpr int kDenseThreads = 512;
 constexpr int kDenseRho = 1000;
-constexpr int kDenseMany = 3072;          // events from which on it is taken for any size of event
-constexpr int kDenseEvents = 768;         // and for events of few hits and votes:
+constexpr int kDenseRows = 1024;
+constexpr int kDenseAny = 1024;           // events from which on local maxima take it whatever an event's size
+constexpr int kDenseAnyNarrow = 3072;     // the same below kDenseRho
+constexpr int kDenseEvents = 768;         // events of few hits and votes:
 constexpr int kDenseHits = 320;
 constexpr int kDenseVotes = 140000;       // hits times theta rows
 constexpr int kBandCall = 64;             // calls of up to this many events may run k_band
@@ -294,7 +303,15 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     const int row_bytes = 4 * c.pitch;
     hough_status st = make_shape(c, g.wg_threads > 0 ? g.wg_threads : 1024, g.tile_rows, lds_max, n_cu, c, why);
     if (st) return st;
-    if (g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2 && g.n_rho >= kDenseRho) {
+    // rows too long for sixteen waves' buffers and a hot set: as many waves as
+    // have room for both, or every event would take the tiled path (768 events of
+    // 272 hits on 2048 x 2048 bins: 2328 -> 425 us)
+    for (int t = 512; t >= 256 && g.wg_threads == 0 && g.tile_rows == 0 && g.peak_mode != 2 && !c.stream_ok; t /= 2) {
+        std::string none;
+        Shape f;
+        if (make_shape(c, t, 0, lds_max, n_cu, f, none) == HOUGH_OK && f.stream_ok) static_cast<Shape &>(c) = f;
+    }
+    if (g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2) {
         std::string none;
         Shape f;
         if (make_shape(c, kDenseThreads, 0, lds_max / 2, n_cu, f, none) == HOUGH_OK && f.stream_ok && f.big_ok &&
@@ -388,8 +405,9 @@ void free_workspace(Workspace &w) {
 // Whether a call of n_events events with n_hits hits in all takes the dense shape.
 bool takes_dense(const Ctx &c, int64_t n_events, int64_t n_hits) {
     if (c.dense.max_resident == 0 || n_events < kDenseEvents) return false;
-    return n_events >= kDenseMany ||
-           (n_hits <= kDenseHits * n_events && n_hits * c.cfg.n_theta <= kDenseVotes * n_events);
+    const bool wide = c.cfg.n_rho >= kDenseRho;
+    if (c.cfg.peak_mode == 1 && c.cfg.n_theta <= kDenseRows && n_events >= (wide ? kDenseAny : kDenseAnyNarrow)) return true;
+    return wide && n_hits <= kDenseHits * n_events && n_hits * c.cfg.n_theta <= kDenseVotes * n_events;
 }
 
 size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, char *base, Workspace *w, bool dense) {

@@ -749,3 +749,16 @@ def test_large_argmax_rows_by_pairs(gpu_available, kw):
     kw = dict(peak_mode=0, max_iters=6, **kw)
     _, want = check_batch(b, "large argmax %s" % kw, **kw)
     check_repeated(b, want, 90, kw)
+
+
+@pytest.mark.parametrize("kw", [{"n_rho": 1700}, {"n_rho": 2048}, {"n_rho": 4000}, {"n_rho": 2048, "peak_mode": 0, "max_iters": 8},
+                                {"n_rho": 2048, "nms_radius": 2}, {"n_rho": 2048, "sweep_groups": 2}, {"n_rho": 9000}])
+def test_long_rows_take_fewer_waves(gpu_available, kw):
+    # rows of more bins than sixteen waves' buffers and a hot set leave room
+    # for: a shape of fewer waves that streams rows (2048, 4000), or the
+    # tiled path where none does (9000); one event, a few, and many
+    b = eventgen.make_batch([eventgen.pileup_event(57_000 + i, n_tracks=n) for i, n in enumerate((4, 50, 110, 150))])
+    kw = dict(n_theta=200, rho_min=-750.0, rho_max=750.0, **kw) if kw["n_rho"] > 4000 else dict(n_theta=200, **kw)
+    _, want = check_batch(b, "long rows %s" % kw, **kw)
+    check_batch(eventgen.make_batch([b.events[1]]), "long rows alone %s" % kw, **kw)
+    check_repeated(b, want, 66, kw)
