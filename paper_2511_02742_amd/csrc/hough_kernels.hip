@@ -66,8 +66,12 @@ constexpr int kClaimBlockW = 8;  // alive-hit words up to which claims are resol
 // hits, and its hot set often outgrows LDS there, so that it was done for
 // nothing. With the line at no hits / 384 / 320 / 256: 256 pileup-70 events 346 /
 // 242 / 243 / 243 us, 512 pileup-60 events at two per CU 454 / 350 / 297 / 299,
-// 1024 pileup-50 events 408 / 395 / 400 / 449.
+// 1024 pileup-50 events 408 / 395 / 400 / 449. On few rows the hot set holds such
+// an event's bins and the band's fixed costs show (512 pileup-45 events at two per CU
+// row by row / banded: 96 / 113 us on 180 rows, 133 / 141 on 360, 208 / 166 on 512,
+// 291 / 222 on 720): from kBandRows rows on.
 constexpr int kBandHits = 352;
+constexpr int kBandRows = 512;
 constexpr int kSegCounts = 128;  // vote counts T .. T + 127 ordered by order_segments
 
 __device__ __forceinline__ int wave_id() {
@@ -2826,7 +2830,8 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
     int n_hs = 0;          // entries of the hot set
     bool hs_valid = false; // the hot set holds every bin >= T of the current histogram
     // alive hits above which the first iteration's sweep is banded
-    int band_from = A.g_hs == nullptr && A.big_ok != 0 && band_scan_ok<false>(A, kBandHits) && band_ring_ok<NT>(A, kBandHits, 0)
+    int band_from = A.g_hs == nullptr && A.n_theta >= kBandRows && A.big_ok != 0 &&
+                            band_scan_ok<false>(A, kBandHits) && band_ring_ok<NT>(A, kBandHits, 0)
                         ? kBandHits
                         : kChunks * kWave;
     bool big = false;      // large-event path this iteration: peaks in a device-memory slot
