@@ -762,3 +762,33 @@ def test_long_rows_take_fewer_waves(gpu_available, kw):
     _, want = check_batch(b, "long rows %s" % kw, **kw)
     check_batch(eventgen.make_batch([b.events[1]]), "long rows alone %s" % kw, **kw)
     check_repeated(b, want, 66, kw)
+
+
+@pytest.mark.parametrize("n_events", [1, 63, 64, 1023, 1024, 1025, 4095, 4096, 4097, 8193, 20000])
+def test_prefix_sums_of_event_counts(gpu_available, n_events):
+    # output offsets and the summed statistics over calls at the edges of the
+    # scan's rounds (1024 events) and loads (4096), empty events among them
+    pool = [eventgen.make_event(58_000 + i, n) for i, n in enumerate((1, 3, 6, 2, 4, 9, 1))]
+    kw = dict(n_theta=64, n_rho=128)
+    rng = np.random.default_rng(n_events)
+    pick = rng.integers(0, len(pool) + 1, n_events)
+    one = []
+    for ev in pool:
+        c, h, info = run_batch(finder(**kw), eventgen.make_batch([ev]))
+        one.append((c, h, info["iters"]))
+    zs = [ev.z for ev in pool] + [np.zeros(0, np.float32)]
+    vs = [ev.vane for ev in pool] + [np.zeros(0, np.int16)]
+    one.append((one[0][0][:0], one[0][1][:0], 0))
+    off = np.concatenate([[0], np.cumsum([len(zs[i]) for i in pick])]).astype(np.int64)
+    b = eventgen.Batch(r=np.zeros(off[-1], np.float32), z=np.concatenate([zs[i] for i in pick]),
+                       vane=np.concatenate([vs[i] for i in pick]), offsets=off, events=[])
+    cand, hits, info = run_batch(finder(**kw), b)
+    want = np.concatenate([one[i][0] for i in pick])
+    assert info["status"] == 0 and len(cand) == len(want)
+    assert np.array_equal(cand["event"], np.repeat(np.arange(n_events), [len(one[i][0]) for i in pick]))
+    assert np.array_equal(cand["hit_offset"], np.concatenate([[0], np.cumsum(want["n_hits"])])[:-1])
+    for f in FIELDS:
+        assert f in ("event", "hit_offset") or np.array_equal(cand[f], want[f]), f
+    assert np.array_equal(hits, np.concatenate([one[i][1] for i in pick]))
+    assert info["iters"] == sum(one[i][2] for i in pick)
+    assert info["max_iters"] == max(one[i][2] for i in pick)
