@@ -792,3 +792,26 @@ def test_prefix_sums_of_event_counts(gpu_available, n_events):
     assert np.array_equal(hits, np.concatenate([one[i][1] for i in pick]))
     assert info["iters"] == sum(one[i][2] for i in pick)
     assert info["max_iters"] == max(one[i][2] for i in pick)
+
+
+@pytest.mark.parametrize("kw", [{}, {"min_votes": 1}, {"min_votes": 3}, {"n_theta": 1}, {"n_theta": 17, "n_rho": 33}, {"n_theta": 1023, "n_rho": 999},
+                                {"wg_threads": 256, "tile_rows": 8}, {"peak_mode": 0}, {"n_theta": 2047, "sweep_groups": 3}])
+def test_sweep_of_few_hits_by_half_waves(gpu_available, kw):
+    # at most 32 hits: a wave sweeps two of its rows at a time, one per half;
+    # 0 .. 34 hits, odd numbers of rows per wave, lines whose hits all share
+    # a bin in every row's half
+    rng = np.random.default_rng(59)
+    evs = [(np.zeros(0, np.float32), np.zeros(0, np.int16))]
+    for n in list(range(1, 8)) + [15, 16, 17, 31, 32, 33, 34]:
+        ev = eventgen.pileup_event(59_000 + n, n_tracks=n // 3 + 12)
+        evs.append((ev.z[:n], ev.vane[:n]))
+        evs.append((np.full(n, 12.5, np.float32), np.full(n, 3, np.int16)))
+        evs.append((np.linspace(-60.0, 60.0, n).astype(np.float32), rng.integers(0, 40, n).astype(np.int16)))
+    off = np.concatenate([[0], np.cumsum([len(z) for z, _ in evs])]).astype(np.int64)
+    b = eventgen.Batch(r=np.zeros(off[-1], np.float32), z=np.concatenate([z for z, _ in evs]),
+                       vane=np.concatenate([v for _, v in evs]), offsets=off, events=[])
+    got, want = check_batch(b, "few hits %s" % kw, **kw)
+    assert len(want.cand) > 0
+    for z, v in evs[3::9]:
+        one = eventgen.Batch(r=np.zeros(len(z), np.float32), z=z, vane=v, offsets=np.array([0, len(z)], np.int64), events=[])
+        check_batch(one, "few hits alone %s" % kw, **kw)
