@@ -1597,7 +1597,8 @@ __device__ __forceinline__ unsigned long long band_scan(const FindArgs &A, const
 // cleared for row j + 1. Same peaks as band_big with w = 1, but wave w
 // writes its peaks to its own segment pk[w * big_pk / NW ...] in flat-index
 // order and leaves their number in rc[3] (rc[4] set: the segment overflowed);
-// argmax mode takes the largest key of the listed bins instead.
+// argmax mode takes the largest key of the listed bins instead. Rows
+// of up to 1024 bins go to band_scan; the rings serve longer ones.
 template <int NT, bool MAX>
 __device__ __forceinline__ void band_ring(const FindArgs &A, const float2 *__restrict__ cs, const Lds &L,
                                           const HitRegs &h, const float2 *xh, int nx, int n_alive,
@@ -3295,9 +3296,10 @@ __global__ __launch_bounds__(NT) void k_sweep(FindArgs A, const float2 *__restri
 
 // First banded sweep of the large events of a small call, spread over nwf
 // workgroups per event: workgroup g sweeps the rows the finder's wave g
-// would (band_ring's partition), with every hit of the event in LDS, in
-// band_ring's 16-bit three-row rings with the direct window test (its waves
-// split the band again; each wave keeps its own rings, lists and peaks).
+// would (band_ring's partition), with every hit of the event in LDS, two rows
+// at a time (band_scan) or, for rows of more than 1024 bins, in band_ring's 16-bit
+// three-row rings with the direct window test (its waves split the band again;
+// each wave keeps its own row buffer or rings, lists and peaks).
 // The band's peaks, in flat order, go to segment g of the event's slot (slot
 // e of the pool, reserved here; the finder's workgroup of event e takes it
 // over), their number to b_cnt[e * nwf + g], and each workgroup that
