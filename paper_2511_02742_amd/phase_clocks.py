@@ -56,7 +56,7 @@ def main():
         rows.append((name, per))
 
     b50 = eventgen.pileup_batch(4096)
-    run("4096 pileup-50 events, 1024 threads, 30-row tile", HoughFinder(0), b50)
+    run("4096 pileup-50 events, 1024 threads, 30-row tile", HoughFinder(0, wg_threads=1024), b50)
     run("4096 pileup-50 events, 512 threads, 14-row tile", HoughFinder(0, wg_threads=512, tile_rows=14), b50)
     f = HoughFinder(0)
     for pile in (50, 100, 150):
