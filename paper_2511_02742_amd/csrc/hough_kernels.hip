@@ -1077,11 +1077,20 @@ __device__ __forceinline__ int acquire_slot(const FindArgs &A, Shared &sh) {
     return sh.slot;
 }
 
+// Waits for this wave's stores and cache write-backs to reach the L2 and memory.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Every wave waits for its own stores before the barrier: the barrier does not
+// (within a workgroup the L1 orders them), and the one write-back of the L2
+// covers only what has arrived there. A store that came later would stay in this
+// XCD's L2 and could overwrite the slot's next owner in memory.
 __device__ __forceinline__ void release_slot(const FindArgs &A, int s) {
     if (s < 0) return;
+    stores_done();
     __syncthreads();
     if (tid_x() == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        stores_done();   // (the compiler leaves this one out where it knows of no store in flight)
         atomicExch(&A.pool_flags[s], 0);
     }
 }
