@@ -104,6 +104,9 @@ struct Shared {
     int wtot[16];
 };
 
+// Hits are 32-bit positions below 2^31 - 1. A lane's position or the next round's
+// may pass the end by up to a workgroup's width, so scans count unsigned.
+
 // A window's hits in LDS, by vane (in hit order inside a vane is not kept: the
 // choice of a hit does not depend on the order). Position p holds hit q = bq[p]
 // of the window; r is NaN once the hit is in a track (no gate takes it).
@@ -206,8 +209,8 @@ __device__ int extend(const TwArgs &A, const Window &W, int kid, End &E, int &n,
         uint32_t score = 0xffffffffu, q = 0xffffffffu;
         int pos = 0;
         float rb = 0.0f, zb = 0.0f, tb = 0.0f;
-        const int s = STAGED ? W.vst[target] : 0, e = STAGED ? W.vst[target + 1] : W.m;
-        for (int i = s + lane(); i < e; i += 64) {
+        const uint32_t s = STAGED ? W.vst[target] : 0, e = STAGED ? W.vst[target + 1] : W.m;
+        for (uint32_t i = s + lane(); i < e; i += 64) {
             if (!STAGED && (A.used[W.wa + i] >= 0 || A.vane[W.wa + i] != target)) continue;
             const float r = STAGED ? W.r[i] : A.r[W.wa + i];
             const float z = STAGED ? W.z[i] : A.z[W.wa + i];
@@ -215,11 +218,11 @@ __device__ int extend(const TwArgs &A, const Window &W, int kid, End &E, int &n,
             const float dr = fabsf(r - r_hat), dz = fabsf(z - z_hat), dt = fabsf(t - E.t);
             if (dr <= A.gate_r && dz <= A.gate_z && dt <= A.gate_t) {
                 const uint32_t sc = __float_as_uint(dr + dz);
-                const uint32_t qi = STAGED ? (uint32_t)W.bq[i] : (uint32_t)i;
+                const uint32_t qi = STAGED ? (uint32_t)W.bq[i] : i;
                 if (sc < score || (sc == score && qi < q)) {
                     score = sc;
                     q = qi;
-                    pos = i;
+                    pos = (int)i;
                     rb = r;
                     zb = z;
                     tb = t;
@@ -437,8 +440,8 @@ __device__ void seed(const TwArgs &A, const FindArgs &F, const Window &W, Shared
 // time (one wave).
 __device__ __forceinline__ int advance_lb(const float *t, int from, int end, float x) {
     for (;;) {
-        const int i = from + lane();
-        const int c = __popcll(__ballot(i < end && t[i] < x));
+        const uint32_t i = (uint32_t)from + lane();
+        const int c = __popcll(__ballot(i < (uint32_t)end && t[i] < x));
         from += c;
         if (c < 64) return from;
     }
@@ -454,9 +457,9 @@ __device__ __forceinline__ void next_window(const TwArgs &A, uint32_t min_votes,
     bool unused = false, load = true;
     while (w < A.n_windows) {
         if (load) {
-            const int i = cb + lane();
-            tl = i < end ? A.t[i] : __int_as_float(0x7f800000);
-            unused = i < end && A.used[i] < 0;
+            const uint32_t i = (uint32_t)cb + lane();
+            tl = i < (uint32_t)end ? A.t[i] : __int_as_float(0x7f800000);
+            unused = i < (uint32_t)end && A.used[i] < 0;
             load = false;
         }
         const float lo = (float)w * A.step_ns, hi = lo + A.window_ns;
@@ -508,9 +511,9 @@ __device__ __forceinline__ void next_window(const TwArgs &A, uint32_t min_votes,
 template <int NT>
 __device__ __forceinline__ int collect(const TwArgs &A, Shared &T, int wa, int we, int64_t base) {
     int n = 0;
-    for (int h0 = wa; h0 < we; h0 += NT) {
-        const int h = h0 + tid();
-        const bool take = h < we && A.used[h] < 0;
+    for (uint32_t h0 = wa; h0 < (uint32_t)we; h0 += NT) {
+        const uint32_t h = h0 + tid();
+        const bool take = h < (uint32_t)we && A.used[h] < 0;
         const unsigned long long m = __ballot(take);
         if (lane() == 0) T.wtot[wave()] = __popcll(m);
         __syncthreads();
@@ -524,7 +527,7 @@ __device__ __forceinline__ int collect(const TwArgs &A, Shared &T, int wa, int w
             const int64_t o = base + n + before + __popcll(m & ((1ull << lane()) - 1ull));
             A.wz[o] = A.z[h];
             A.wv[o] = A.vane[h];
-            A.widx[o] = h;
+            A.widx[o] = (int)h;
         }
         n += all;
         __syncthreads();
