@@ -306,6 +306,7 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     // rows too long for sixteen waves' buffers and a hot set: as many waves as
     // have room for both, or every event would take the tiled path (768 events of
     // 272 hits on 2048 x 2048 bins: 2328 -> 425 us)
+    const bool long_rows = !c.stream_ok;
     for (int t = 512; t >= 256 && g.wg_threads == 0 && g.tile_rows == 0 && g.peak_mode != 2 && !c.stream_ok; t /= 2) {
         std::string none;
         Shape f;
@@ -332,8 +333,12 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     c.sweep_threads = g.sweep_threads > 0 ? g.sweep_threads : 256;
     if (c.sweep_groups > 0) {
         const int sl = hough::sweep_lds_bytes(c.sweep_threads, c.pitch);
-        if (sl + kStaticLds > lds_max) { why = "sweep row buffers do not fit in LDS"; return HOUGH_ERR_INVALID_ARG; }
-        if (hough::set_sweep_lds_limit(c.sweep_threads, sl) != hipSuccess) {
+        if (sl + kStaticLds > lds_max && long_rows) {
+            c.sweep_groups = 0;   // as on the tiled path, which such rows would take with sixteen waves
+        } else if (sl + kStaticLds > lds_max) {
+            why = "sweep row buffers do not fit in LDS";
+            return HOUGH_ERR_INVALID_ARG;
+        } else if (hough::set_sweep_lds_limit(c.sweep_threads, sl) != hipSuccess) {
             why = "hipFuncSetAttribute failed for the sweep kernel";
             return HOUGH_ERR_DEVICE;
         }

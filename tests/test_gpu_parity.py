@@ -815,3 +815,13 @@ def test_sweep_of_few_hits_by_half_waves(gpu_available, kw):
     for z, v in evs[3::9]:
         one = eventgen.Batch(r=np.zeros(len(z), np.float32), z=z, vane=v, offsets=np.array([0, len(z)], np.int64), events=[])
         check_batch(one, "few hits alone %s" % kw, **kw)
+
+
+@pytest.mark.parametrize("n_rho", [1536, 2048, 3000, 4096])
+@pytest.mark.parametrize("threads", [256, 1024])
+def test_long_rows_with_a_configured_split_sweep(gpu_available, n_rho, threads):
+    # rows too long for sixteen waves: the split runs where its row buffers fit
+    # and is left out where they do not (1024 threads from some 2450 bins on)
+    b = eventgen.make_batch([eventgen.pileup_event(62_000 + i, n_tracks=n) for i, n in enumerate((3, 20, 60, 110))])
+    kw = dict(n_theta=256, n_rho=n_rho, sweep_groups=2, sweep_threads=threads)
+    check_batch(b, "split sweep on long rows %s" % kw, **kw)
