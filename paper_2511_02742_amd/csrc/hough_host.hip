@@ -92,10 +92,15 @@ constexpr int kSmallCall = 8;
 // the hot set, and one that does not fit costs a sweep per peak: only events
 // of few hits and votes take the shape (1024 events of 275 hits on 180 rows
 // 237 / 146, on 1024 rows 450 / 2401).
-// The host knows the events' number and mean size, not the largest: a few events
-// that dwarf the rest end their call later in it (1 % of 200 tracks among 768 of 10
-// on 180 rows 492 / 629).
-constexpr int kDenseThreads = 512;
+// The host knows the events' number and mean size, not the largest, and a few
+// events that dwarf the rest end their call later in it (1 % of 200 tracks among 768
+// of 10 on 180 rows 486 / 613), or outgrow its shorter lists and are swept tile by
+// tile (one of 300 among them: 580 / 20871). So such a call enqueues both
+// shapes, and k_order_pick, which reads every event's size anyway, picks one: this
+// one if no event has more hits than dense_hits() says. The other launch's
+// workgroups end at once, 3 us of a call (4096 Poisson(20) events 455 -> 458, 1024
+// argmax events of 50 tracks 134 -> 137).
+using hough::kDenseThreads;
 constexpr int kDenseRho = 1000;
 constexpr int kDenseRows = 1024;
 constexpr int kDenseAny = 1024;           // events from which on local maxima take it whatever an event's size
@@ -103,6 +108,8 @@ constexpr int kDenseAnyNarrow = 3072;     // the same below kDenseRho
 constexpr int kDenseEvents = 768;         // events of few hits and votes:
 constexpr int kDenseHits = 320;
 constexpr int kDenseVotes = 140000;       // hits times theta rows
+constexpr int kDenseCalm = 352;           // events of up to this many hits end no call much later (in it, their
+constexpr int kDenseCalmRows = 512;       // first sweep is not banded); on fewer rows than this, of up to 512 hits
 constexpr int kBandCall = 64;             // calls of up to this many events may run k_band
 constexpr int kTwCfLds = 48 << 10;        // LDS the time-sliced finder takes at least in mode 2 (windows of about 2000 hits)
 constexpr int64_t kRegisterHits = 512;    // alive hits the finder holds in registers
@@ -407,9 +414,31 @@ void free_workspace(Workspace &w) {
     w = Workspace();
 }
 
-// Whether a call of n_events events with n_hits hits in all takes the dense shape.
+// The most hits that an event of a dense call may have: its list holds them, and
+// the event is small, or less than about twice what a workgroup takes on average.
+// Default / dense (us) by the largest event's share of that average:
+//   0.6    2048 events of 1 to 150 tracks, 1024 rows   1451 / 1105
+//   1.1    4096, 10 % of 150 tracks among 10           1071 / 841
+//   1.4    4096, 1 % of 100 tracks among 10            576 / 381
+//   1.8    4096, 1 % of 60 tracks among 5              440 / 284
+//   2.1    2048, 10 % of 150 tracks among 10           552 / 713
+//   2.7    4096, 1 % of 200 tracks among 10            644 / 873
+//   3.9    2048, 1 % of 60 tracks among 5              237 / 245
+//   7.4    768, 1 % of 100 tracks among 10             269 / 356
+// and with no event of more than kDenseCalm hits
+//   2.6    2048, 1 % of 40 tracks among 5              226 / 151
+//   6.0    768, 1 % of 40 tracks among 5               102 / 101 (180 rows 73 / 58)
+int64_t dense_hits(const Ctx &c, int64_t n_hits) {
+    const int64_t list = kRegisterHits + std::min(c.dense.hs_cap & ~63, 56 * 64);
+    if (c.cfg.peak_mode == 0) return list;
+    const int64_t calm = c.cfg.n_theta < kDenseCalmRows ? kRegisterHits : kDenseCalm;
+    return std::min(list, std::max(calm, 19 * n_hits / (10 * c.dense.max_resident)));
+}
+
+// Whether a call of n_events events with n_hits hits in all may take the dense shape.
 bool takes_dense(const Ctx &c, int64_t n_events, int64_t n_hits) {
     if (c.dense.max_resident == 0 || n_events < kDenseEvents) return false;
+    if (n_hits > n_events * dense_hits(c, n_hits)) return false;   // some event has more than it may
     const bool wide = c.cfg.n_rho >= kDenseRho;
     if (c.cfg.peak_mode == 1 && c.cfg.n_theta <= kDenseRows && n_events >= (wide ? kDenseAny : kDenseAnyNarrow)) return true;
     return wide && n_hits <= kDenseHits * n_events && n_hits * c.cfg.n_theta <= kDenseVotes * n_events;
@@ -435,6 +464,7 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
     const size_t o_pflags = take(4 * ((size_t)slots + 2 * kBandCall));
     const size_t o_bcnt = take(4 * (size_t)kBandCall * 16);
     const size_t o_pool = take((size_t)slots * (size_t)slot_bytes);
+    const size_t o_pick = dense ? take(sizeof(hough::Pick)) : 0;
     if (base != nullptr) {
         w->base = base;
         w->bytes = off;
@@ -466,6 +496,7 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
         w->pool_slots = slots;
         w->slot_bytes = slot_bytes;
         w->big_pk = big_pk;
+        w->pick = dense ? reinterpret_cast<hough::Pick *>(base + o_pick) : nullptr;
     }
     return off;
 }
@@ -502,6 +533,20 @@ hough_status ensure_workspace(const Ctx &c, Workspace &w, int64_t n_hits, int64_
     return HOUGH_OK;
 }
 
+// The arguments that go with a launch shape.
+void set_shape(hough::FindArgs &a, const Shape &f) {
+    a.tile_rows = f.tile_rows;
+    a.tile_bytes = f.tile_bytes;
+    a.stream_ok = f.stream_ok;
+    a.hs_cap = f.hs_cap;
+    a.hs_off = f.hs_off;
+    a.sorted_off = f.sorted_off;
+    a.big_sort = f.big_sort;
+    a.big_ok = f.big_ok;
+    a.roll_off = f.roll_off;
+    a.roll_bytes = f.roll_bytes;
+}
+
 hough::FindArgs find_args(const Ctx &c, const Shape &f, const Workspace &w) {
     hough::FindArgs a{};
     const hough_config &g = c.cfg;
@@ -531,16 +576,11 @@ hough::FindArgs find_args(const Ctx &c, const Shape &f, const Workspace &w) {
     a.ev_stats = w.ev_stats;
     a.order = nullptr;
     a.err = w.err;
-    a.tile_rows = f.tile_rows;
+    set_shape(a, f);
     a.pitch = c.pitch;
-    a.tile_bytes = f.tile_bytes;
     a.hcap = kHotCap;
     a.pkeep = kPeakKeep;
-    a.stream_ok = f.stream_ok;
     a.safe_r2 = c.safe_r2;
-    a.hs_cap = f.hs_cap;
-    a.hs_off = f.hs_off;
-    a.sorted_off = f.sorted_off;
     a.g_cnt = w.g_cnt;
     a.g_flag = w.g_flag;
     a.g_hs = (c.sweep_groups > 0 && c.stream_ok) ? w.g_hs : nullptr;
@@ -548,10 +588,6 @@ hough::FindArgs find_args(const Ctx &c, const Shape &f, const Workspace &w) {
     a.pool_flags = w.pool_flags;
     a.pool_slots = w.pool_slots;
     a.big_pk = w.big_pk;
-    a.big_sort = f.big_sort;
-    a.big_ok = f.big_ok;
-    a.roll_off = f.roll_off;
-    a.roll_bytes = f.roll_bytes;
     a.slot_bytes = w.slot_bytes;
     a.ccs = c.d_ccs;
     a.inv_wc = c.inv_wc;
@@ -572,8 +608,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
                           bool longest_first) {
     // (the served form's launches overlap on the device and keep the default
     // shape; so does a workspace without a slot for each dense workgroup)
-    const bool dense = longest_first && takes_dense(c, n_events, n_total) &&
-                       w.pool_slots >= std::min<int64_t>(n_events, c.dense.max_resident);
+    const bool dense = longest_first && w.pick != nullptr && takes_dense(c, n_events, n_total);
     const Shape &f = dense ? c.dense : c;
     hough::FindArgs a = find_args(c, f, w);
     a.n_events = n_events;
@@ -582,6 +617,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     a.z = z;
     a.vane = vane;
     a.max_iters = max_iters;
+    if (c.ev_clock != nullptr && n_events <= c.ev_clock_events) a.ev_clock = c.ev_clock;
     const bool single = n_events == 1;
     // k_band: a call of a few tens of events sweeps its large events' first
     // band ahead of the finder, over one workgroup per finder wave each
@@ -617,23 +653,38 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
         hipError_t sb = hough::launch_band(a, f.wg_threads / 64, c.band_lds, s);
         if (sb != hipSuccess) return fail(&c, HOUGH_ERR_DEVICE, std::string("band launch failed: ") + hipGetErrorString(sb));
     }
-    if (longest_first && n_events > std::max(f.max_resident, kOrderMin)) {
+    hough::FindArgs list{};
+    if (longest_first && (dense || n_events > std::max(f.max_resident, kOrderMin))) {
         // the longest events start first and the short ones fill the CUs at
         // the end of the launch (with no more events than resident
         // workgroups every event starts at once and the order is moot)
-        hipError_t so = hough::launch_order(offsets, n_events, w.order, s);
-        if (so != hipSuccess) return fail(&c, HOUGH_ERR_DEVICE, std::string("order launch failed: ") + hipGetErrorString(so));
+        hipError_t so;
         a.order = w.order;
+        if (dense) {
+            list = a;
+            set_shape(list, c);
+            so = hough::launch_order_pick(list, w.order, w.pick, dense_hits(c, n_total), s);
+            a.pick = w.pick;
+        } else {
+            so = hough::launch_order(offsets, n_events, w.order, s);
+        }
+        if (so != hipSuccess) return fail(&c, HOUGH_ERR_DEVICE, std::string("order launch failed: ") + hipGetErrorString(so));
     }
-    if (c.ev_clock != nullptr && n_events <= c.ev_clock_events) a.ev_clock = c.ev_clock;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed && n_events > 0) {
         if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
             return fail(&c, HOUGH_ERR_DEVICE, "hipEventCreate failed");
         (void)hipEventRecord(e0, s);
     }
-    hipError_t st = c.cfg.peak_mode == 2 ? hough::launch_find_cf(a, c.wg_threads, c.lds_bytes, s)
-                                         : hough::launch_find(a, f.wg_threads, f.lds_bytes, s);
+    hipError_t st;
+    if (c.cfg.peak_mode == 2) {
+        st = hough::launch_find_cf(a, c.wg_threads, c.lds_bytes, s);
+    } else if (dense) {
+        st = hough::launch_dense(a, f.lds_bytes, s);
+        if (st == hipSuccess) st = hough::launch_list(list, w.pick, c.max_resident, c.wg_threads, c.lds_bytes, s);
+    } else {
+        st = hough::launch_find(a, f.wg_threads, f.lds_bytes, s);
+    }
     if (st != hipSuccess) return fail(&c, HOUGH_ERR_DEVICE, std::string("finder launch failed: ") + hipGetErrorString(st));
     if (e0) {
         (void)hipEventRecord(e1, s);

@@ -3240,6 +3240,40 @@ __device__ __noinline__ void find_event_call(const FindArgs *A, int e, int64_t b
     find_event<NT, MAX>(a, a.cs, find_lds(a), sh, __builtin_amdgcn_readfirstlane(e), uniform64(b), uniform64(n));
 }
 
+// The dense shape of a call that enqueues two: k_order_pick's choice decides. (In
+// k_find the test cost calls of one shape 1 %: the compiler held other values.)
+template <bool MAX>
+__global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_dense(FindArgs A,
+                                                                                               const float2 *__restrict__ cs) {
+    __shared__ Shared sh;
+    if (A.pick->dense == 0) return;
+    const int e = __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]);
+    const int64_t b = uniform64(A.offsets[e]);
+    find_event<kDenseThreads, MAX>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
+}
+
+// The events of a call that k_order_pick sent past the dense shape, the longest
+// first, by as many workgroups as are resident at once (k_find with a workgroup per
+// event in its place cost a call that takes the dense shape 10 us at 4096 events,
+// this 3; where it runs, its event function being a call, it takes 1 to 4 % longer).
+template <int NT, bool MAX>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_list(Pick *P) {
+    if (P->dense != 0) return;
+    __shared__ int at;
+    const FindArgs &A = tw::const_args(&P->list);
+    for (;;) {
+        if (tid_x() == 0) at = atomicAdd(&P->next, 1);
+        __syncthreads();
+        const int i = __builtin_amdgcn_readfirstlane(at);
+        __syncthreads();
+        if (i >= A.n_events) return;
+        const int e = __builtin_amdgcn_readfirstlane(A.order[i]);
+        const int64_t b = uniform64(A.offsets[e]);
+        find_event_call<NT, MAX>(&P->list, e, b, uniform64(A.offsets[e + 1]) - b);
+        __syncthreads();
+    }
+}
+
 // The window loop of the time-sliced finder: one workgroup per timeline, which
 // runs find_event on each window that needs it (see hough_tw.h). Workgroups of
 // the finder's own shape, so no more are resident at once than it has
@@ -3684,18 +3718,30 @@ hipError_t launch_band(const FindArgs &a, int nwf, int band_lds, hipStream_t s) 
 // does not depend on it.
 constexpr int kOrderBins = 1024;
 
-__global__ __launch_bounds__(kOrderBins) void k_order(const int64_t *offsets, int32_t n_events, int32_t *order) {
+template <bool PICK>
+__device__ __forceinline__ void order_events(const int64_t *offsets, int32_t n_events, int32_t *order, Pick *pick,
+                                             int64_t pick_hits) {
     __shared__ int cur[kOrderBins];
     __shared__ int wsum[kOrderBins / kWave];
     const int t = tid_x();
+    int over = 0;
     cur[t] = 0;
     __syncthreads();
     for (int e = t; e < n_events; e += kOrderBins) {
         const int64_t n = offsets[e + 1] - offsets[e];
         const int k = n <= 0 ? 0 : (n >= kOrderBins - 1 ? kOrderBins - 1 : (int)n);
         atomicAdd(&cur[kOrderBins - 1 - k], 1);
+        if (PICK) over |= n > pick_hits ? 1 : 0;
     }
-    __syncthreads();
+    if (PICK) {
+        over = __syncthreads_or(over);
+        if (t == 0) {
+            pick->dense = over ? 0 : 1;
+            pick->next = 0;
+        }
+    } else {
+        __syncthreads();
+    }
     // bucket starts: exclusive scan over the buckets
     const int v = cur[t];
     const int incl = wave_incl_scan(v);
@@ -3710,6 +3756,16 @@ __global__ __launch_bounds__(kOrderBins) void k_order(const int64_t *offsets, in
         const int k = n <= 0 ? 0 : (n >= kOrderBins - 1 ? kOrderBins - 1 : (int)n);
         order[atomicAdd(&cur[kOrderBins - 1 - k], 1)] = e;
     }
+}
+
+__global__ __launch_bounds__(kOrderBins) void k_order(const int64_t *offsets, int32_t n_events, int32_t *order) {
+    order_events<false>(offsets, n_events, order, nullptr, 0);
+}
+
+// The same, and which of the call's two shapes runs.
+__global__ __launch_bounds__(kOrderBins) void k_order_pick(FindArgs list, int32_t *order, Pick *pick, int64_t pick_hits) {
+    if (tid_x() == 0) pick->list = list;
+    order_events<true>(list.offsets, list.n_events, order, pick, pick_hits);
 }
 
 // Clears the words every finder call expects at zero: the error words, the
@@ -3732,6 +3788,11 @@ __global__ void k_clear_ws(long long *err, int32_t *g_cnt, int32_t *g_flag, int6
 hipError_t launch_order(const int64_t *offsets, int32_t n_events, int32_t *order, hipStream_t s) {
     if (n_events <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_order, dim3(1), dim3(kOrderBins), 0, s, offsets, n_events, order);
+    return hipGetLastError();
+}
+
+hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, hipStream_t s) {
+    hipLaunchKernelGGL(k_order_pick, dim3(1), dim3(kOrderBins), 0, s, list, order, pick, pick_hits);
     return hipGetLastError();
 }
 
@@ -3784,8 +3845,18 @@ hipError_t lds_limit(const void *f, int lds_bytes) {
 
 hipError_t set_find_lds_limit(int wg_threads, int lds_bytes) {
     return with_threads(wg_threads, [&](auto nt) {
-        const hipError_t e = lds_limit(reinterpret_cast<const void *>(k_find<nt()>), lds_bytes);
-        return e != hipSuccess ? e : lds_limit(reinterpret_cast<const void *>(k_argmax<nt()>), lds_bytes);
+        if (nt() == kDenseThreads)
+            for (const void *f : {reinterpret_cast<const void *>(k_dense<false>), reinterpret_cast<const void *>(k_dense<true>)}) {
+                const hipError_t e = lds_limit(f, lds_bytes);
+                if (e != hipSuccess) return e;
+            }
+        for (const void *f : {reinterpret_cast<const void *>(k_find<nt()>), reinterpret_cast<const void *>(k_argmax<nt()>),
+                              reinterpret_cast<const void *>(k_list<nt(), false>),
+                              reinterpret_cast<const void *>(k_list<nt(), true>)}) {
+            const hipError_t e = lds_limit(f, lds_bytes);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     });
 }
 
@@ -3818,6 +3889,24 @@ hipError_t launch_find(const FindArgs &a, int wg_threads, int lds_bytes, hipStre
             hipLaunchKernelGGL(k_argmax<nt()>, dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
         else
             hipLaunchKernelGGL(k_find<nt()>, dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_dense(const FindArgs &a, int lds_bytes, hipStream_t s) {
+    if (a.peak_mode == 0)
+        hipLaunchKernelGGL(k_dense<true>, dim3(a.n_events), dim3(kDenseThreads), lds_bytes, s, a, a.cs);
+    else
+        hipLaunchKernelGGL(k_dense<false>, dim3(a.n_events), dim3(kDenseThreads), lds_bytes, s, a, a.cs);
+    return hipGetLastError();
+}
+
+hipError_t launch_list(const FindArgs &list, Pick *pick, int groups, int wg_threads, int lds_bytes, hipStream_t s) {
+    return with_threads(wg_threads, [&](auto nt) {
+        if (list.peak_mode == 0)
+            hipLaunchKernelGGL((k_list<nt(), true>), dim3(groups), dim3(nt()), lds_bytes, s, pick);
+        else
+            hipLaunchKernelGGL((k_list<nt(), false>), dim3(groups), dim3(nt()), lds_bytes, s, pick);
         return hipGetLastError();
     });
 }

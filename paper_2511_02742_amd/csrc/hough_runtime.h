@@ -44,6 +44,7 @@ struct Workspace {
     int32_t pool_words = 0;
     int64_t slot_bytes = 0;
     int32_t big_pk = 0;        // peak entries per slot list
+    Pick *pick = nullptr;      // which of a call's two launches runs (workspaces with the dense shape's slots)
 };
 
 // A launch shape of the finder and the LDS layout that goes with it.

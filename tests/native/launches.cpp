@@ -97,6 +97,20 @@ hipError_t launch_order(const int64_t *, int32_t n, int32_t *, hipStream_t) {
     note("{\"launch\": \"order\", \"events\": %d}", n);
     return hipSuccess;
 }
+hipError_t launch_order_pick(const FindArgs &a, int32_t *, Pick *, int64_t hits, hipStream_t) {
+    note("{\"launch\": \"order_pick\", \"events\": %d, \"hits\": %lld}", a.n_events, (long long)hits);
+    return hipSuccess;
+}
+hipError_t launch_dense(const FindArgs &a, int lds, hipStream_t) {
+    note("{\"launch\": \"dense\", \"lds\": %d, \"rows\": %d, \"hs_cap\": %d, \"events\": %d, \"ordered\": %d, \"slots\": %d}", lds,
+         a.tile_rows, a.hs_cap, a.n_events, a.order != nullptr, a.pool_slots);
+    return hipSuccess;
+}
+hipError_t launch_list(const FindArgs &a, Pick *, int groups, int threads, int lds, hipStream_t) {
+    note("{\"launch\": \"list\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"groups\": %d, \"slots\": %d}", threads, lds,
+         a.tile_rows, groups, a.pool_slots);
+    return hipSuccess;
+}
 hipError_t launch_compact(const CompactArgs &a, hipStream_t) {
     note("{\"launch\": \"compact\", \"ordered\": %d}", a.ordered);
     return hipSuccess;

@@ -825,3 +825,41 @@ def test_long_rows_with_a_configured_split_sweep(gpu_available, n_rho, threads):
     b = eventgen.make_batch([eventgen.pileup_event(62_000 + i, n_tracks=n) for i, n in enumerate((3, 20, 60, 110))])
     kw = dict(n_theta=256, n_rho=n_rho, sweep_groups=2, sweep_threads=threads)
     check_batch(b, "split sweep on long rows %s" % kw, **kw)
+
+
+@pytest.mark.parametrize("kw,n_events,sizes", [
+    (dict(n_theta=180, n_rho=1000), 768, (352, 353, 512, 513, 1536, 1537, 1650, 2560)),
+    (dict(n_theta=180, n_rho=1000, peak_mode=0, max_iters=6), 768, (512, 513, 1536, 1537)),
+    (dict(), 1024, (352, 353, 2560, 2561)),
+])
+def test_a_large_event_among_many_small_ones(gpu_available, kw, n_events, sizes):
+    # calls of many events whose shape is chosen on the device, from the largest
+    # event: on both sides of the sizes where the choice turns. Whichever shape runs, no
+    # event outgrows its lists (a tiled sweep) and the bytes are the one-per-CU
+    # shape's: eager, again with another largest event, and captured
+    import torch
+    from paper_2511_02742_amd.hough import HoughFinder
+    small = [eventgen.pileup_event(63_000 + i, n_tracks=10) for i in range(48)]
+    big = eventgen.pileup_event(63_100, n_tracks=560)
+    assert big.n_hits >= max(sizes)
+    rng = np.random.default_rng(n_events)
+    own, one = finder(**kw), finder(wg_threads=1024, **kw)
+    dev = torch.device("cuda", 0)
+    for n in sizes:
+        evs = [(small[i].z, small[i].vane) for i in rng.integers(0, len(small), n_events)]
+        evs[int(rng.integers(0, n_events))] = (big.z[:n], big.vane[:n])
+        off = np.concatenate([[0], np.cumsum([len(z) for z, _ in evs])]).astype(np.int64)
+        t = [torch.from_numpy(x).to(dev) for x in (np.concatenate([z for z, _ in evs]), np.concatenate([v for _, v in evs]), off)]
+        got, want = own.find(*t).to_host(), one.find(*t).to_host()
+        assert got[2]["status"] == want[2]["status"] == 0 and got[2]["candidates"] == want[2]["candidates"] > 0
+        assert got[0].tobytes() == want[0].tobytes() and np.array_equal(got[1], want[1]), n
+        assert got[2]["iters"] == want[2]["iters"] and got[2]["tiled"] == 0 == want[2]["tiled"], (n, got[2])
+    graph = HoughFinder(0, **kw).capture(*t)
+    for _ in range(3):
+        graph.out.cand.zero_()
+        own.find(*t)
+        rep = graph.launch()
+        torch.cuda.synchronize()
+        r = rep.to_host()
+        assert r[0].tobytes() == want[0].tobytes() and np.array_equal(r[1], want[1])
+    graph.close()

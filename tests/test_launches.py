@@ -68,3 +68,78 @@ def test_a_split_sweep_does_not_refuse_a_grid(host, n_rho, threads):
     st, h = host.create(n_rho=n_rho, sweep_groups=2, sweep_threads=threads)
     assert st == 0
     host.lib.hough_destroy(h)
+
+
+NMS, ARGMAX = 1, 0
+
+
+# The dense shape's rule at its edges: (configuration, events, hits, most hits of
+# an event in it, or None where the call enqueues the context's shape alone).
+DENSE = [
+    ({}, 767, 767 * 27, None),
+    ({}, 768, 768 * 27, 352),                         # small events: 352 hits, whatever the mean
+    ({}, 768, 768 * 136, 387),                        # else 1.9 times what a workgroup takes on average
+    ({}, 768, 768 * 137, None),                       # hits times rows
+    ({}, 1024, 1024 * 137, 520),                      # from 1024 events on whatever they hold,
+    ({}, 1024, 1024 * 600, 2280),
+    ({}, 1024, 1024 * 1100, 2560),                    # up to the shape's list of hits
+    ({}, 1024, 1024 * 2560, 2560),
+    ({}, 1024, 1024 * 2560 + 1, None),                # some event has more
+    ({}, 1023, 1023 * 137, None),
+    ({"n_theta": 1025}, 1024, 1024 * 137, None),
+    ({"n_theta": 1025}, 1024, 1024 * 100, 380),
+    ({"n_rho": 999}, 3071, 3071 * 27, None),
+    ({"n_rho": 999}, 3072, 3072 * 27, 352),
+    ({"n_rho": 1000, "n_theta": 180}, 768, 768 * 320, 912),
+    ({"n_rho": 1000, "n_theta": 180}, 768, 768 * 321, None),
+    ({"n_rho": 1000, "n_theta": 180}, 768, 768 * 27, 512),     # on few rows events of up to 512 hits are small
+    ({"n_rho": 1000, "n_theta": 511}, 768, 768 * 27, 512),
+    ({"n_rho": 1000, "n_theta": 512}, 768, 768 * 27, 352),
+    ({"n_rho": 1000, "n_theta": 180}, 4096, 4096 * 400, 1536),
+    ({"n_rho": 1000, "n_theta": 180, "peak_mode": ARGMAX}, 768, 768 * 27, 1536),
+    ({"n_rho": 1000, "n_theta": 180, "peak_mode": ARGMAX}, 4096, 4096 * 321, None),
+    ({"wg_threads": 1024}, 4096, 4096 * 110, None),
+    ({"tile_rows": 14}, 4096, 4096 * 110, None),
+    ({"sweep_groups": 1}, 4096, 4096 * 110, None),
+    ({"nms_radius": 3}, 4096, 4096 * 110, 1672),
+    ({"n_rho": 1000, "n_theta": 180, "peak_mode": 2}, 4096, 4096 * 110, None),
+]
+
+
+@pytest.mark.parametrize("cfg,events,hits,most", DENSE)
+def test_dense_shape(host, cfg, events, hits, most):
+    """A call that may take the dense shape enqueues it and, for the choice made on
+    the device, the context's own; every other call the context's alone."""
+    got = host.calls(events, hits, **cfg)
+    kinds = [x["launch"] for x in got]
+    if most is None:
+        assert kinds[-2] in ("find", "find_cf") and "order_pick" not in kinds and "dense" not in kinds
+        return
+    assert kinds == ["order_pick", "dense", "list", "compact"]
+    order, dense, rest, compact = got
+    assert order["hits"] == most and order["events"] == dense["events"] == events
+    assert compact["ordered"] == dense["ordered"] == 1
+    # two workgroups per CU, a slot for each; the other shape is the context's own
+    assert dense["lds"] <= (160 << 10) // 2 - 2048 and rest["threads"] == 1024 and rest["groups"] == 256
+    assert dense["slots"] == min(events, 512)
+    # no event that the choice lets in outgrows the shape's list
+    assert most <= 512 + min(dense["hs_cap"] // 64 * 64, 56 * 64)
+
+
+def test_dense_shape_needs_its_workspace(host):
+    """Without memory for the dense shape's slots, and in the fixed scratch, a call
+    takes the context's own shape; a captured one has its own workspace."""
+    try:
+        host.lib.set_memory(200 << 20)   # the slots of one workgroup per CU are 128 MiB, of two 256
+        assert [x["launch"] for x in host.calls(1024, 1024 * 110)] == ["order", "find", "compact"]
+    finally:
+        host.lib.set_memory(1 << 40)
+    assert [x["launch"] for x in host.calls(1024, 1024 * 110, noalloc=True)] == ["order", "find", "compact"]
+    st, h = host.create()
+    g = ctypes.c_void_p()
+    host.log()
+    n = 1024 * 110
+    assert host.lib.hough_graph_create(h, 1024, n, FAKE, FAKE, FAKE, FAKE, n, FAKE, n, FAKE, ctypes.byref(g)) == 0
+    assert [x["launch"] for x in host.log()] == ["order_pick", "dense", "list", "compact"]
+    host.lib.hough_graph_destroy(g)
+    host.lib.hough_destroy(h)
