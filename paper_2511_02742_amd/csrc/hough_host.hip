@@ -100,7 +100,7 @@ constexpr int kSmallCall = 8;
 // one if no event has more hits than dense_hits() says. The other launch's
 // workgroups end at once, 3 us of a call (4096 Poisson(20) events 455 -> 458, 1024
 // argmax events of 50 tracks 134 -> 137).
-using hough::kDenseThreads;
+constexpr int kDenseThreads = 512;
 constexpr int kDenseRho = 1000;
 constexpr int kDenseRows = 1024;
 constexpr int kDenseAny = 1024;           // events from which on local maxima take it whatever an event's size
@@ -317,7 +317,12 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     for (int t = 512; t >= 256 && g.wg_threads == 0 && g.tile_rows == 0 && g.peak_mode != 2 && !c.stream_ok; t /= 2) {
         std::string none;
         Shape f;
-        if (make_shape(c, t, 0, lds_max, n_cu, f, none) == HOUGH_OK && f.stream_ok) static_cast<Shape &>(c) = f;
+        if (make_shape(c, t, 0, lds_max, n_cu, f, none) == HOUGH_OK && f.stream_ok) {
+            // (an event that outgrows the hot set's list is swept tile by tile here
+            // too, and slower by fewer waves: such calls keep the sixteen)
+            c.wide = c;
+            static_cast<Shape &>(c) = f;
+        }
     }
     if (g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2) {
         std::string none;
@@ -368,7 +373,9 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     // the time-sliced finder stages a window's hits in the finder's LDS
     // between its calls
     c.tw_lds = c.lds_bytes;
-    if (g.peak_mode != 2 && hough::set_tw_lds_limit(c.wg_threads, c.tw_lds) != hipSuccess) {
+    if (g.peak_mode != 2 && (hough::set_tw_lds_limit(c.wg_threads, c.tw_lds) != hipSuccess ||
+                             (c.wide.max_resident > 0 &&
+                              hough::set_tw_lds_limit(c.wide.wg_threads, c.wide.lds_bytes) != hipSuccess))) {
         why = "hipFuncSetAttribute failed for the time-sliced finder";
         return HOUGH_ERR_DEVICE;
     }
@@ -414,6 +421,9 @@ void free_workspace(Workspace &w) {
     w = Workspace();
 }
 
+// The most alive hits that shape f keeps on chip; the tiled path takes the others.
+int64_t list_hits(const Shape &f) { return kRegisterHits + std::min(f.hs_cap & ~63, 56 * 64); }
+
 // The most hits that an event of a dense call may have: its list holds them, and
 // the event is small, or less than about twice what a workgroup takes on average.
 // Default / dense (us) by the largest event's share of that average:
@@ -429,7 +439,7 @@ void free_workspace(Workspace &w) {
 //   2.6    2048, 1 % of 40 tracks among 5              226 / 151
 //   6.0    768, 1 % of 40 tracks among 5               102 / 101 (180 rows 73 / 58)
 int64_t dense_hits(const Ctx &c, int64_t n_hits) {
-    const int64_t list = kRegisterHits + std::min(c.dense.hs_cap & ~63, 56 * 64);
+    const int64_t list = list_hits(c.dense);
     if (c.cfg.peak_mode == 0) return list;
     const int64_t calm = c.cfg.n_theta < kDenseCalmRows ? kRegisterHits : kDenseCalm;
     return std::min(list, std::max(calm, 19 * n_hits / (10 * c.dense.max_resident)));
@@ -444,7 +454,8 @@ bool takes_dense(const Ctx &c, int64_t n_events, int64_t n_hits) {
     return wide && n_hits <= kDenseHits * n_events && n_hits * c.cfg.n_theta <= kDenseVotes * n_events;
 }
 
-size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, char *base, Workspace *w, bool dense) {
+size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, char *base, Workspace *w, bool dense,
+                        bool bare) {
     const int64_t ncand = nh / (int64_t)c.cfg.min_votes + 1;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
@@ -454,7 +465,7 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
     const size_t o_evst = take(8 * (size_t)hough::kEvStats * ne), o_err = take(8 * 4), o_offs = take(8 * 4);
     const size_t o_gcnt = take(4 * ne), o_gflag = take(4 * ne), o_order = take(4 * ne);
     // split-sweep hot lists: one per event, or one for the one-event split
-    const int64_t ghs_events = c.sweep_groups > 0 ? ne : (c.single_split ? std::min<int64_t>(ne, kSmallCall) : 0);
+    const int64_t ghs_events = c.sweep_groups > 0 ? ne : (c.single_split && !bare ? std::min<int64_t>(ne, kSmallCall) : 0);
     const size_t o_ghs = ghs_events > 0 ? take(8 * (size_t)ghs_events * (size_t)std::max(c.hs_cap, 1)) : 0;
     // large-event slots: no more workgroups than events, nor than fit the
     // device at once, hold one at a time
@@ -464,7 +475,8 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
     const size_t o_pflags = take(4 * ((size_t)slots + 2 * kBandCall));
     const size_t o_bcnt = take(4 * (size_t)kBandCall * 16);
     const size_t o_pool = take((size_t)slots * (size_t)slot_bytes);
-    const size_t o_pick = dense ? take(sizeof(hough::Pick)) : 0;
+    const bool pick = dense || (c.wide.max_resident > 0 && ne > 1 && !bare);
+    const size_t o_pick = pick ? take(sizeof(hough::Pick)) : 0;
     if (base != nullptr) {
         w->base = base;
         w->bytes = off;
@@ -496,7 +508,8 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
         w->pool_slots = slots;
         w->slot_bytes = slot_bytes;
         w->big_pk = big_pk;
-        w->pick = dense ? reinterpret_cast<hough::Pick *>(base + o_pick) : nullptr;
+        w->dense = dense;
+        w->pick = pick ? reinterpret_cast<hough::Pick *>(base + o_pick) : nullptr;
     }
     return off;
 }
@@ -583,7 +596,7 @@ hough::FindArgs find_args(const Ctx &c, const Shape &f, const Workspace &w) {
     a.safe_r2 = c.safe_r2;
     a.g_cnt = w.g_cnt;
     a.g_flag = w.g_flag;
-    a.g_hs = (c.sweep_groups > 0 && c.stream_ok) ? w.g_hs : nullptr;
+    a.g_hs = (c.sweep_groups > 0 && f.stream_ok) ? w.g_hs : nullptr;
     a.pool = w.pool;
     a.pool_flags = w.pool_flags;
     a.pool_slots = w.pool_slots;
@@ -608,8 +621,13 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
                           bool longest_first) {
     // (the served form's launches overlap on the device and keep the default
     // shape; so does a workspace without a slot for each dense workgroup)
-    const bool dense = longest_first && w.pick != nullptr && takes_dense(c, n_events, n_total);
-    const Shape &f = dense ? c.dense : c;
+    const bool dense = longest_first && w.dense && takes_dense(c, n_events, n_total);
+    // long rows: events that outgrow the shape's list, if there are any. Alone, the
+    // host knows; among others the device does (or the tiled shape takes all)
+    const bool wide = c.wide.max_resident > 0 && n_total > list_hits(c);
+    const bool pick = dense || (wide && n_events > 1 && w.pick != nullptr);
+    const Shape &f = dense ? c.dense : (wide && !pick ? c.wide : c);
+    const Shape &other = dense ? c : c.wide;
     hough::FindArgs a = find_args(c, f, w);
     a.n_events = n_events;
     a.n_total = n_total;
@@ -621,7 +639,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     const bool single = n_events == 1;
     // k_band: a call of a few tens of events sweeps its large events' first
     // band ahead of the finder, over one workgroup per finder wave each
-    const bool band = n_events > 0 && n_events <= kBandCall && c.band_split && c.sweep_groups == 0 &&
+    const bool band = n_events > 0 && n_events <= kBandCall && c.band_split && c.sweep_groups == 0 && f.stream_ok &&
                       w.pool_slots >= n_events && n_total > kBandMinHits;
     a.band_min = band ? (int32_t)kBandMinHits : (int32_t)kRegisterHits;
     if (single) {
@@ -629,7 +647,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
         a.cand_ws = cand;
         a.hits_ws = hit_index;
     }
-    if (n_events > 0 && n_events <= kSmallCall && c.single_split && a.g_hs == nullptr) {
+    if (n_events > 0 && n_events <= kSmallCall && c.single_split && f.stream_ok && w.g_hs != nullptr) {
         // a few events: each one's first sweep spread over several workgroups
         // (the sweep kernel takes events of up to band_min hits; a lone
         // larger event skips it)
@@ -654,16 +672,18 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
         if (sb != hipSuccess) return fail(&c, HOUGH_ERR_DEVICE, std::string("band launch failed: ") + hipGetErrorString(sb));
     }
     hough::FindArgs list{};
-    if (longest_first && (dense || n_events > std::max(f.max_resident, kOrderMin))) {
+    const bool ordered = longest_first && (dense || n_events > std::max(f.max_resident, kOrderMin));
+    if (ordered || pick) {
         // the longest events start first and the short ones fill the CUs at
         // the end of the launch (with no more events than resident
         // workgroups every event starts at once and the order is moot)
         hipError_t so;
         a.order = w.order;
-        if (dense) {
+        if (pick) {
             list = a;
-            set_shape(list, c);
-            so = hough::launch_order_pick(list, w.order, w.pick, dense_hits(c, n_total), s);
+            list.g_hs = nullptr;
+            set_shape(list, other);
+            so = hough::launch_order_pick(list, w.order, w.pick, dense ? dense_hits(c, n_total) : list_hits(c), s);
             a.pick = w.pick;
         } else {
             so = hough::launch_order(offsets, n_events, w.order, s);
@@ -679,9 +699,10 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     hipError_t st;
     if (c.cfg.peak_mode == 2) {
         st = hough::launch_find_cf(a, c.wg_threads, c.lds_bytes, s);
-    } else if (dense) {
-        st = hough::launch_dense(a, f.lds_bytes, s);
-        if (st == hipSuccess) st = hough::launch_list(list, w.pick, c.max_resident, c.wg_threads, c.lds_bytes, s);
+    } else if (pick) {
+        st = hough::launch_picked(a, f.wg_threads, f.lds_bytes, s);
+        if (st == hipSuccess)
+            st = hough::launch_list(list, w.pick, other.max_resident, other.wg_threads, other.lds_bytes, s);
     } else {
         st = hough::launch_find(a, f.wg_threads, f.lds_bytes, s);
     }
@@ -707,7 +728,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     ca.cand = cand;
     ca.hit_index = hit_index;
     ca.counts = counts;
-    ca.ordered = a.order != nullptr ? 1 : 0;
+    ca.ordered = ordered ? 1 : 0;
     if (hough::launch_compact(ca, s) != hipSuccess) return fail(&c, HOUGH_ERR_DEVICE, "compaction launch failed");
     return HOUGH_OK;
 }
@@ -885,7 +906,10 @@ hough_status hough_find_noalloc(hough_ctx *ctx, void *stream, int32_t n_events, 
     if (base == nullptr)
         return fail(c, HOUGH_ERR_DEVICE, std::string("scratch address lookup failed: ") + hipGetErrorString(se));
     const int64_t nh = std::max<int64_t>(n_hits_total, 1), ne = std::max<int32_t>(n_events, 1);
-    const size_t need = layout_workspace(*c, nh, ne, kNoAllocBigPk, nullptr, nullptr);
+    size_t need = layout_workspace(*c, nh, ne, kNoAllocBigPk, nullptr, nullptr);
+    // what only the shape for long rows adds is left out where it does not fit
+    const bool bare = c->wide.max_resident > 0 && need > (size_t)HOUGH_NOALLOC_SCRATCH_BYTES;
+    if (bare) need = layout_workspace(*c, nh, ne, kNoAllocBigPk, nullptr, nullptr, false, true);
     if (need > (size_t)HOUGH_NOALLOC_SCRATCH_BYTES) {
         char msg[160];
         snprintf(msg, sizeof msg, "%lld hits in %d events need %zu bytes of scratch; the scratch holds %zu",
@@ -894,7 +918,7 @@ hough_status hough_find_noalloc(hough_ctx *ctx, void *stream, int32_t n_events, 
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     Workspace w;
-    layout_workspace(*c, nh, ne, kNoAllocBigPk, base, &w);
+    layout_workspace(*c, nh, ne, kNoAllocBigPk, base, &w, false, bare);
     // the scratch holds whatever the last call left there: clear the words
     // the finder expects at zero
     if (hough::launch_clear_workspace(w.err, w.g_cnt, w.g_flag, ne, w.pool_flags, w.pool_words, s) != hipSuccess)

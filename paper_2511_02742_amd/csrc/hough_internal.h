@@ -124,9 +124,10 @@ __device__ inline void stamp_event(const FindArgs &A, int e, unsigned long long 
     }
 }
 
-// A call's choice between the dense shape and the context's own, made on the device.
+// The choice between a call's two shapes, made on the device: the first unless an
+// event has too many hits for it.
 struct Pick {
-    int32_t dense;   // 1: k_dense runs, 0: k_list (the context's own shape)
+    int32_t first;   // 1: k_picked runs, 0: k_list
     int32_t next;    // k_list: the next event's place in order[]
     FindArgs list;   // its arguments
 };
@@ -161,9 +162,6 @@ struct CompactArgs {
     int32_t ordered;  // the finder ran the events longest first (counts[HOUGH_COUNT_ORDERED])
 };
 
-// threads of the dense shape's workgroups (two per CU)
-constexpr int kDenseThreads = 512;
-
 // LDS bytes the host leaves beside a kernel's dynamic LDS for its static
 // shared variables (the finder's per-workgroup state is the largest)
 constexpr int kStaticLds = 2048;
@@ -184,14 +182,14 @@ int sweep_lds_bytes(int threads, int pitch);
 hipError_t launch_clear_workspace(long long *err, int32_t *g_cnt, int32_t *g_flag, int64_t n_events,
                                   int32_t *pool_flags, int32_t slots, hipStream_t s);
 // order[0, n_events): the events by descending hit count (device offsets). With
-// pick, also the choice of a call's shape: dense if no event has more than
+// pick, also the choice of a call's shape: the first if no event has more than
 // pick_hits hits; list are k_list's arguments.
 hipError_t launch_order(const int64_t *offsets, int32_t n_events, int32_t *order, hipStream_t s);
 hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, hipStream_t s);
-// The finder on a's events, in a.order, if a.pick is the dense shape.
-hipError_t launch_dense(const FindArgs &a, int lds_bytes, hipStream_t s);
-// The finder on list's events unless k_order picked the dense shape: `groups`
-// workgroups that take one event after the other.
+// The finder on a's events, in a.order, if the first shape was picked (256 or 512 threads).
+hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, hipStream_t s);
+// The finder on list's events, in list.order, if it was not: `groups` workgroups
+// that take one event after the other.
 hipError_t launch_list(const FindArgs &list, Pick *pick, int groups, int wg_threads, int lds_bytes, hipStream_t s);
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s);
 hipError_t launch_dump(const DumpArgs &a, int lds_bytes, hipStream_t s);

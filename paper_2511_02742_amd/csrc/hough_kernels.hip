@@ -3240,25 +3240,26 @@ __device__ __noinline__ void find_event_call(const FindArgs *A, int e, int64_t b
     find_event<NT, MAX>(a, a.cs, find_lds(a), sh, __builtin_amdgcn_readfirstlane(e), uniform64(b), uniform64(n));
 }
 
-// The dense shape of a call that enqueues two: k_order_pick's choice decides. (In
-// k_find the test cost calls of one shape 1 %: the compiler held other values.)
-template <bool MAX>
-__global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_dense(FindArgs A,
-                                                                                               const float2 *__restrict__ cs) {
+// The first of the two shapes of a call that enqueues both: k_order_pick's choice
+// decides. (In k_find the test cost calls of one shape 1 %: the compiler held other
+// values.)
+template <int NT, bool MAX>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_picked(FindArgs A,
+                                                                                     const float2 *__restrict__ cs) {
     __shared__ Shared sh;
-    if (A.pick->dense == 0) return;
+    if (A.pick->first == 0) return;
     const int e = __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]);
     const int64_t b = uniform64(A.offsets[e]);
-    find_event<kDenseThreads, MAX>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
+    find_event<NT, MAX>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
 }
 
-// The events of a call that k_order_pick sent past the dense shape, the longest
+// The events of a call that k_order_pick sent past the first shape, the longest
 // first, by as many workgroups as are resident at once (k_find with a workgroup per
 // event in its place cost a call that takes the dense shape 10 us at 4096 events,
 // this 3; where it runs, its event function being a call, it takes 1 to 4 % longer).
 template <int NT, bool MAX>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_list(Pick *P) {
-    if (P->dense != 0) return;
+    if (P->first != 0) return;
     __shared__ int at;
     const FindArgs &A = tw::const_args(&P->list);
     for (;;) {
@@ -3736,7 +3737,7 @@ __device__ __forceinline__ void order_events(const int64_t *offsets, int32_t n_e
     if (PICK) {
         over = __syncthreads_or(over);
         if (t == 0) {
-            pick->dense = over ? 0 : 1;
+            pick->first = over ? 0 : 1;
             pick->next = 0;
         }
     } else {
@@ -3845,8 +3846,9 @@ hipError_t lds_limit(const void *f, int lds_bytes) {
 
 hipError_t set_find_lds_limit(int wg_threads, int lds_bytes) {
     return with_threads(wg_threads, [&](auto nt) {
-        if (nt() == kDenseThreads)
-            for (const void *f : {reinterpret_cast<const void *>(k_dense<false>), reinterpret_cast<const void *>(k_dense<true>)}) {
+        if constexpr (nt() < 1024)
+            for (const void *f : {reinterpret_cast<const void *>(k_picked<nt(), false>),
+                                  reinterpret_cast<const void *>(k_picked<nt(), true>)}) {
                 const hipError_t e = lds_limit(f, lds_bytes);
                 if (e != hipSuccess) return e;
             }
@@ -3893,12 +3895,17 @@ hipError_t launch_find(const FindArgs &a, int wg_threads, int lds_bytes, hipStre
     });
 }
 
-hipError_t launch_dense(const FindArgs &a, int lds_bytes, hipStream_t s) {
-    if (a.peak_mode == 0)
-        hipLaunchKernelGGL(k_dense<true>, dim3(a.n_events), dim3(kDenseThreads), lds_bytes, s, a, a.cs);
-    else
-        hipLaunchKernelGGL(k_dense<false>, dim3(a.n_events), dim3(kDenseThreads), lds_bytes, s, a, a.cs);
-    return hipGetLastError();
+hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, hipStream_t s) {
+    auto launch = [&](auto nt) {
+        if (a.peak_mode == 0)
+            hipLaunchKernelGGL((k_picked<nt(), true>), dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
+        else
+            hipLaunchKernelGGL((k_picked<nt(), false>), dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
+        return hipGetLastError();
+    };
+    if (wg_threads == 512) return launch(std::integral_constant<int, 512>());
+    if (wg_threads == 256) return launch(std::integral_constant<int, 256>());
+    return hipErrorInvalidValue;   // sixteen waves are the second shape
 }
 
 hipError_t launch_list(const FindArgs &list, Pick *pick, int groups, int wg_threads, int lds_bytes, hipStream_t s) {

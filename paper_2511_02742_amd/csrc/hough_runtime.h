@@ -44,7 +44,8 @@ struct Workspace {
     int32_t pool_words = 0;
     int64_t slot_bytes = 0;
     int32_t big_pk = 0;        // peak entries per slot list
-    Pick *pick = nullptr;      // which of a call's two launches runs (workspaces with the dense shape's slots)
+    Pick *pick = nullptr;      // which of a call's two launches runs (contexts with a second shape)
+    bool dense = false;        // slots for the dense shape's workgroups
 };
 
 // A launch shape of the finder and the LDS layout that goes with it.
@@ -76,6 +77,7 @@ struct Ctx : Shape {
     int pitch = 0;
     int sweep_groups = 0, sweep_threads = 256;
     Shape dense;                              // two workgroups per CU, for calls of many events (max_resident 0: none)
+    Shape wide;                               // long rows: sixteen waves, for events that outgrow the own shape's list (max_resident 0: none)
     int single_split = 0;                     // calls of a few events split their first sweeps
     int band_split = 0, band_lds = 0;         // and their large events' first banded sweeps (k_band)
     int big_pk = 0;                           // peak entries per large-event slot
@@ -122,9 +124,10 @@ hough_status ensure_workspace(const Ctx &c, Workspace &w, int64_t n_hits, int64_
 // Bytes of a workspace for exactly nh hits and ne events whose large-event
 // slots hold big_pk peak entries per list; with base non-NULL, also points
 // w's arrays into base (the caller clears what must start at zero). dense:
-// slots for as many workgroups as the dense shape has resident.
+// slots for as many workgroups as the dense shape has resident; bare: without the
+// split sweep's lists and the choice between two shapes.
 size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, char *base, Workspace *w,
-                        bool dense = false);
+                        bool dense = false, bool bare = false);
 void free_workspace(Workspace &w);
 // Enqueues one finder call on s (split sweep, finder, compaction); outputs
 // as in hough_find. With longest_first, a call of many events runs its
@@ -136,6 +139,8 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
 // The finder's arguments of context c and shape f on workspace w, but for the
 // call's events, hits and outputs.
 FindArgs find_args(const Ctx &c, const Shape &f, const Workspace &w);
+// The most alive hits that shape f keeps on chip; the tiled path takes the others.
+int64_t list_hits(const Shape &f);
 
 }  // namespace rt
 }  // namespace hough

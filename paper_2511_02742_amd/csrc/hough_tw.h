@@ -38,6 +38,10 @@ struct TwArgs {
     int32_t *widx;                   // global hit index of each window-event hit
     long long *err;                  // [status (min), first bad global hit (min)]
     FindArgs *find;                  // the event finder's arguments, in device memory
+    // calls of two shapes: 1 at *pick when a window holds more than pick_hits hits, and
+    // then the launch whose `mine` is 1 runs, else the other (NULL: this one does)
+    int32_t *pick;
+    int32_t mine, pick_hits;
     // outputs
     hough_track *tracks;
     int32_t *hit_index;
@@ -541,7 +545,7 @@ __device__ __forceinline__ int collect(const TwArgs &A, Shared &T, int wa, int w
 template <int NT, class Find>
 __device__ __forceinline__ void run(const TwArgs &A, const FindArgs &F, uint32_t *lds, Shared &T, const Find &find) {
     // one thread's look at the status: another workgroup may set it meanwhile
-    if (tid() == 0) T.busy = A.err[0] == 0 ? 1 : 0;
+    if (tid() == 0) T.busy = A.err[0] == 0 && (A.pick == nullptr || *A.pick == A.mine) ? 1 : 0;
     __syncthreads();
     if (!T.busy) return;
     const int b = blockIdx.x;

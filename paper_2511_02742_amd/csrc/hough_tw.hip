@@ -45,8 +45,9 @@ __device__ __forceinline__ int lane() { return threadIdx.x & 63; }
 
 __device__ __forceinline__ int64_t slot0(const TwArgs &A, int b, int64_t base) { return base / 3 + b; }
 
-// Clears the tracks, and puts the event finder's arguments in device memory.
-__global__ void k_tw_init(TwArgs A, FindArgs F) {
+// Clears the tracks, and puts the event finder's arguments in device memory (wide:
+// a second shape's behind them, or no more).
+__global__ void k_tw_init(TwArgs A, FindArgs F, FindArgs wide) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < A.n_total; i += stride) {
         A.used[i] = -1;
@@ -62,11 +63,16 @@ __global__ void k_tw_init(TwArgs A, FindArgs F) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         A.err[0] = 0;
         A.err[1] = LLONG_MAX;
-        *A.find = F;
+        A.find[0] = F;
+        if (A.pick != nullptr) {
+            A.find[1] = wide;
+            *A.pick = 0;
+        }
     }
 }
 
-// Offsets, hit fields and the time order of every timeline.
+// Offsets, hit fields and the time order of every timeline, and whether a window
+// may hold more than pick_hits hits.
 __global__ __launch_bounds__(256) void k_tw_validate(TwArgs A) {
     const int b = blockIdx.x;
     const int64_t base = A.offsets[b], end = A.offsets[b + 1];
@@ -85,6 +91,7 @@ __global__ __launch_bounds__(256) void k_tw_validate(TwArgs A) {
             atomicMin(&A.err[0], (long long)HOUGH_ERR_DATA);
             atomicMin(&A.err[1], (long long)i);
         }
+        if (A.pick != nullptr && i + A.pick_hits < end && A.t[i + A.pick_hits] - ti <= A.window_ns) *A.pick = 1;
     }
 }
 
@@ -235,7 +242,7 @@ hough_status hough_tw_find(hough_ctx *ctx, void *stream, const hough_tw_config *
     const size_t o_tlc = take(8 * B), o_tlk = take(8 * B), o_tlh = take(8 * B), o_tlt = take(8 * B),
                  o_tlhb = take(8 * B);
     const size_t o_slots = take(40 * (size_t)nslots);
-    const size_t o_err = take(8 * 4), o_find = take(sizeof(FindArgs));
+    const size_t o_err = take(8 * 4), o_find = take(2 * sizeof(FindArgs)), o_pick = take(4);
     if (off > c->tw_bytes) {
         if (c->tw_base) {
             if (hipStreamSynchronize(s) != hipSuccess) return fail(c, HOUGH_ERR_DEVICE, "hipStreamSynchronize failed");
@@ -294,19 +301,30 @@ hough_status hough_tw_find(hough_ctx *ctx, void *stream, const hough_tw_config *
     A.err = reinterpret_cast<long long *>(base + o_err);
     A.find = reinterpret_cast<FindArgs *>(base + o_find);
     // hits of a window that fit the LDS beside the vane tables (16-bit positions)
-    A.lds_hits = std::max(0, std::min(4096, (c->tw_lds - tw_vane_bytes(A.n_vanes)) / kTwHitBytes)) & ~63;
+    auto lds_hits = [&](int lds) { return std::max(0, std::min(4096, (lds - tw_vane_bytes(A.n_vanes)) / kTwHitBytes)) & ~63; };
+    A.lds_hits = lds_hits(c->tw_lds);
     A.tracks = tracks;
     A.hit_index = hit_index;
     A.counts = counts;
     A.n_windows = n_windows;
     // the windows' events: timeline b's hits from offsets[b] on
-    FindArgs F = find_args(*c, *c, c->ws);
-    F.n_events = (int32_t)B;
-    F.n_total = N;
-    F.total_is_bound = 1;
-    F.z = A.wz;
-    F.vane = A.wv;
-    F.g_hs = nullptr;
+    auto window_args = [&](const Shape &f) {
+        FindArgs F = find_args(*c, f, c->ws);
+        F.n_events = (int32_t)B;
+        F.n_total = N;
+        F.total_is_bound = 1;
+        F.z = A.wz;
+        F.vane = A.wv;
+        F.g_hs = nullptr;
+        return F;
+    };
+    // long rows: the shape of more waves for calls with a window that outgrows
+    // the own shape's list (the device finds out)
+    const bool wide = c->wide.max_resident > 0 && N > list_hits(*c);
+    if (wide) {
+        A.pick = reinterpret_cast<int32_t *>(base + o_pick);
+        A.pick_hits = (int32_t)list_hits(*c);
+    }
 
     auto launched = [&](const char *what) -> hough_status {
         const hipError_t e = hipGetLastError();
@@ -316,14 +334,21 @@ hough_status hough_tw_find(hough_ctx *ctx, void *stream, const hough_tw_config *
     {
         const int64_t m = std::max<int64_t>(std::max<int64_t>(N, B), 1);
         const int grid = (int)std::min<int64_t>((m + 255) / 256, 2048);
-        hipLaunchKernelGGL(k_tw_init, dim3(grid), dim3(256), 0, s, A, F);
+        hipLaunchKernelGGL(k_tw_init, dim3(grid), dim3(256), 0, s, A, window_args(*c), window_args(wide ? c->wide : *c));
         if ((st = launched("k_tw_init"))) return st;
     }
     if (B > 0) {
         hipLaunchKernelGGL(k_tw_validate, dim3((unsigned)B), dim3(256), 0, s, A);
         if ((st = launched("k_tw_validate"))) return st;
-        const hipError_t e = c->cfg.peak_mode == 2 ? launch_tw_run_cf(A, c->wg_threads, c->tw_lds, s)
-                                                   : launch_tw_run(A, c->wg_threads, c->cfg.peak_mode == 0, c->tw_lds, s);
+        hipError_t e = c->cfg.peak_mode == 2 ? launch_tw_run_cf(A, c->wg_threads, c->tw_lds, s)
+                                             : launch_tw_run(A, c->wg_threads, c->cfg.peak_mode == 0, c->tw_lds, s);
+        if (e == hipSuccess && wide) {
+            TwArgs W = A;
+            W.mine = 1;
+            W.find = A.find + 1;
+            W.lds_hits = lds_hits(c->wide.lds_bytes);
+            e = launch_tw_run(W, c->wide.wg_threads, c->cfg.peak_mode == 0, c->wide.lds_bytes, s);
+        }
         if (e != hipSuccess)
             return fail(c, HOUGH_ERR_DEVICE, std::string("k_tw_run launch failed: ") + hipGetErrorString(e));
     }

@@ -101,14 +101,14 @@ hipError_t launch_order_pick(const FindArgs &a, int32_t *, Pick *, int64_t hits,
     note("{\"launch\": \"order_pick\", \"events\": %d, \"hits\": %lld}", a.n_events, (long long)hits);
     return hipSuccess;
 }
-hipError_t launch_dense(const FindArgs &a, int lds, hipStream_t) {
-    note("{\"launch\": \"dense\", \"lds\": %d, \"rows\": %d, \"hs_cap\": %d, \"events\": %d, \"ordered\": %d, \"slots\": %d}", lds,
-         a.tile_rows, a.hs_cap, a.n_events, a.order != nullptr, a.pool_slots);
+hipError_t launch_picked(const FindArgs &a, int threads, int lds, hipStream_t) {
+    note("{\"launch\": \"picked\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"hs_cap\": %d, \"events\": %d, \"slots\": %d}", threads,
+         lds, a.tile_rows, a.hs_cap, a.n_events, a.pool_slots);
     return hipSuccess;
 }
 hipError_t launch_list(const FindArgs &a, Pick *, int groups, int threads, int lds, hipStream_t) {
-    note("{\"launch\": \"list\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"groups\": %d, \"slots\": %d}", threads, lds,
-         a.tile_rows, groups, a.pool_slots);
+    note("{\"launch\": \"list\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"groups\": %d, \"stream_ok\": %d, \"split\": %d}", threads, lds,
+         a.tile_rows, groups, a.stream_ok, a.g_hs != nullptr);
     return hipSuccess;
 }
 hipError_t launch_compact(const CompactArgs &a, hipStream_t) {

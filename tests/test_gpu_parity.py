@@ -863,3 +863,30 @@ def test_a_large_event_among_many_small_ones(gpu_available, kw, n_events, sizes)
         r = rep.to_host()
         assert r[0].tobytes() == want[0].tobytes() and np.array_equal(r[1], want[1])
     graph.close()
+
+
+@pytest.mark.parametrize("kw,list_hits", [(dict(n_theta=64, n_rho=2048), 4096), (dict(n_theta=64, n_rho=2400), 2560),
+                                          (dict(n_theta=64, n_rho=2400, peak_mode=0, max_iters=5), 2560)])
+@pytest.mark.parametrize("n_events", [2, 9, 70, 300])
+def test_large_events_among_others_on_long_rows(gpu_available, kw, list_hits, n_events):
+    # a call on rows too long for sixteen waves that holds an event at the size
+    # its shape's list holds, and one more hit (the device then picks the tiled
+    # shape): the bytes of the one-shape call, also without allocation
+    import torch
+    small = [eventgen.pileup_event(64_000 + i, n_tracks=n) for i, n in enumerate((3, 12, 30, 60, 90))]
+    big = eventgen.pileup_event(64_100, n_tracks=list_hits // 4)
+    assert big.n_hits > list_hits
+    own, one = finder(**kw), finder(wg_threads=1024, **kw)
+    dev = torch.device("cuda", 0)
+    for n in (list_hits, list_hits + 1):
+        evs = [(ev.z, ev.vane) for ev in (small * n_events)[:n_events]]
+        evs[n_events // 2] = (big.z[:n], big.vane[:n])
+        off = np.concatenate([[0], np.cumsum([len(z) for z, _ in evs])]).astype(np.int64)
+        t = [torch.from_numpy(x).to(dev) for x in (np.concatenate([z for z, _ in evs]), np.concatenate([v for _, v in evs]), off)]
+        want = one.find(*t).to_host()
+        assert want[2]["status"] == 0 and want[2]["candidates"] > 0
+        for got in (own.find(*t).to_host(), own.find(*t, noalloc=True).to_host()):
+            assert got[2]["status"] == 0 and got[0].tobytes() == want[0].tobytes() and np.array_equal(got[1], want[1]), n
+            assert got[2]["iters"] == want[2]["iters"]
+        if n_events >= 70:   # every event by the tiled sweep where the large one outgrows the list, else none of the small
+            assert (own.find(*t).to_host()[2]["tiled"] >= n_events) == (n > list_hits)

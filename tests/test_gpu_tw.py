@@ -174,3 +174,19 @@ def test_windows_of_whole_waves(gpu_available, n):
                            span_ns=0.0, t_decay=np.zeros(1), p=np.zeros(1))
     assert tl.t.max() < 10.0
     check(eventgen.make_timeline_batch([tl]), "%d hits" % n, n_windows=4)
+
+
+@pytest.mark.parametrize("peak_mode", [0, 1])
+def test_busy_windows_on_long_rows(gpu_available, peak_mode):
+    # rows too long for sixteen waves: a call whose windows outgrow the list of the
+    # shape that streams them (2560 hits here) is picked for the tiled one on the
+    # device, a quieter call is not; the tracks are the tiled shape's
+    kw = dict(n_theta=24, n_rho=2400, peak_mode=peak_mode, max_iters=20 if peak_mode == 0 else 0)
+    own, one = finder(**kw), finder(wg_threads=1024, **kw)
+    for rate, busy in ((60.0, True), (6.0, False), (60.0, True)):
+        b = eventgen.timeline_batch(3, rate, 20.0, seed0=1900)
+        first = b.t[:b.offsets[1]]
+        assert (np.sum((first >= 5.0) & (first < 15.0)) > 2560) == busy
+        got, want = own.tw_find_host(b), one.tw_find_host(b)
+        assert got[2] == want[2] and want[2]["status"] == 0 and want[2]["tracks"] > 0
+        assert got[0].tobytes() == want[0].tobytes() and np.array_equal(got[1], want[1])

@@ -113,14 +113,14 @@ def test_dense_shape(host, cfg, events, hits, most):
     got = host.calls(events, hits, **cfg)
     kinds = [x["launch"] for x in got]
     if most is None:
-        assert kinds[-2] in ("find", "find_cf") and "order_pick" not in kinds and "dense" not in kinds
+        assert kinds[-2] in ("find", "find_cf") and "order_pick" not in kinds and "picked" not in kinds
         return
-    assert kinds == ["order_pick", "dense", "list", "compact"]
+    assert kinds == ["order_pick", "picked", "list", "compact"]
     order, dense, rest, compact = got
     assert order["hits"] == most and order["events"] == dense["events"] == events
-    assert compact["ordered"] == dense["ordered"] == 1
+    assert compact["ordered"] == 1
     # two workgroups per CU, a slot for each; the other shape is the context's own
-    assert dense["lds"] <= (160 << 10) // 2 - 2048 and rest["threads"] == 1024 and rest["groups"] == 256
+    assert dense["threads"] == 512 and dense["lds"] <= (160 << 10) // 2 - 2048 and rest["threads"] == 1024 and rest["groups"] == 256
     assert dense["slots"] == min(events, 512)
     # no event that the choice lets in outgrows the shape's list
     assert most <= 512 + min(dense["hs_cap"] // 64 * 64, 56 * 64)
@@ -140,6 +140,56 @@ def test_dense_shape_needs_its_workspace(host):
     host.log()
     n = 1024 * 110
     assert host.lib.hough_graph_create(h, 1024, n, FAKE, FAKE, FAKE, FAKE, n, FAKE, n, FAKE, ctypes.byref(g)) == 0
-    assert [x["launch"] for x in host.log()] == ["order_pick", "dense", "list", "compact"]
+    assert [x["launch"] for x in host.log()] == ["order_pick", "picked", "list", "compact"]
     host.lib.hough_graph_destroy(g)
     host.lib.hough_destroy(h)
+
+
+# Long rows: (rho bins, threads of the shape that streams them, hits its list holds)
+LONG = [(1160, 512, 2560), (2048, 512, 4096), (2304, 512, 4096), (2400, 256, 2560), (4096, 256, 4096)]
+
+
+@pytest.mark.parametrize("n_rho,threads,most", LONG)
+@pytest.mark.parametrize("mode", [NMS, ARGMAX])
+def test_large_events_on_long_rows(host, n_rho, threads, most, mode):
+    """An event that outgrows the list of the shape for long rows is swept tile
+    by tile in either shape, and faster by sixteen waves: alone the host sends it there,
+    a call that may hold one enqueues both shapes."""
+    def of(events, hits, **kw):
+        return [x for x in host.calls(events, hits, n_rho=n_rho, peak_mode=mode, **kw) if x["launch"] not in ("sweep", "band")]
+    # alone, up to the list's size and past it
+    assert [x["threads"] for x in of(1, most)] == [threads]
+    assert [(x["threads"], x["stream_ok"]) for x in of(1, most + 1)] == [(1024, 0)]
+    # a few that cannot hold one, and some that may
+    assert [x["launch"] for x in of(4, most)] == ["find", "compact"]
+    for n in (2, 64, 65, 300):
+        got = of(n, most + 1)
+        assert [x["launch"] for x in got] == ["order_pick", "picked", "list", "compact"]
+        assert got[0]["hits"] == most and got[1]["threads"] == threads and got[1]["hs_cap"] // 64 * 64 >= most - 512
+        assert got[2]["threads"] == 1024 and got[2]["stream_ok"] == 0 and got[2]["split"] == 0
+        assert got[3]["ordered"] == (1 if n > 256 else 0)
+    # where the choice does not fit the fixed scratch, the tiled shape takes the call
+    assert [x["launch"] for x in of(64, most + 1, noalloc=True)] == ["order_pick", "picked", "list", "compact"]
+    # configured shapes are what they were
+    assert [x["threads"] for x in of(1, most + 1, wg_threads=256) + of(2, most + 1, wg_threads=512)[:1]] == [256, 512]
+
+
+@pytest.mark.parametrize("n_rho", [1024, 1160, 2048, 4096])
+@pytest.mark.parametrize("events", [1, 2, 8, 9])
+def test_scratch_limit_of_the_call_without_allocation(host, n_rho, events):
+    """The fixed scratch takes the calls it took when long rows had the tiled
+    shape: what the other shape adds to the workspace is left out where it does
+    not fit."""
+    def fits(hits, **kw):
+        st, h = host.create(n_rho=n_rho, **kw)
+        r = host.lib.hough_find_noalloc(h, None, events, hits, FAKE, FAKE, FAKE, FAKE, hits, FAKE, hits, FAKE)
+        host.lib.hough_destroy(h)
+        return r == 0
+    def most(**kw):
+        lo, hi = 1, 1 << 24
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if fits(mid, **kw) else (lo, mid)
+        return lo
+    tiled = dict(wg_threads=1024) if n_rho > 1152 else {}
+    assert most() >= most(**tiled)
