@@ -7,9 +7,11 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <new>
 #include <string>
+#include <tuple>
 #include <utility>
 #include <vector>
 
@@ -219,6 +221,32 @@ void build_tables(Ctx &c) {
     }
 }
 
+// The dynamic LDS that a kernel's launches may ask for is one setting of the process
+// per device, which every context's shapes share: it is only ever raised, by the
+// shapes that a context takes.
+enum LdsKernel { kLdsFind, kLdsTw, kLdsCf, kLdsTwCf, kLdsSweep, kLdsBand, kLdsDump };
+template <class Set>
+hipError_t raise_lds_limit(const Ctx &c, LdsKernel kernel, int threads, int bytes, Set set) {
+    static std::mutex mu;
+    static std::map<std::tuple<int, int, int>, int> limit;
+    std::lock_guard<std::mutex> g(mu);
+    int &now = limit[{c.device, (int)kernel, threads}];
+    if (bytes <= now) return hipSuccess;
+    const hipError_t e = set();
+    if (e == hipSuccess) now = bytes;
+    return e;
+}
+hipError_t raise_find_limit(const Ctx &c, const Shape &f) {
+    return raise_lds_limit(c, kLdsFind, f.wg_threads, f.lds_bytes,
+                           [&] { return hough::set_find_lds_limit(f.wg_threads, f.lds_bytes); });
+}
+hipError_t raise_tw_limit(const Ctx &c, int threads, int bytes) {
+    return raise_lds_limit(c, kLdsTw, threads, bytes, [&] { return hough::set_tw_lds_limit(threads, bytes); });
+}
+hipError_t raise_sweep_limit(const Ctx &c, int threads, int bytes) {
+    return raise_lds_limit(c, kLdsSweep, threads, bytes, [&] { return hough::set_sweep_lds_limit(threads, bytes); });
+}
+
 // The shape of `threads` per workgroup with LDS tiles of tile_rows own rows (0:
 // as many as fit, in multiples of the waves together with the 2w halo rows, since
 // each wave owns whole rows) in lds_max bytes, next to the hot list and the
@@ -252,10 +280,6 @@ hough_status make_shape(const Ctx &c, int threads, int tile_rows, int lds_max, i
     f.tile_bytes = (f.tile_bytes + 15) & ~15;
     f.lds_bytes = f.tile_bytes + hough::find_lds_extra(f.wg_threads, kHotCap, kPeakKeep);
     if (f.lds_bytes + kStaticLds > lds_max) { why = "LDS budget exceeded"; return HOUGH_ERR_INVALID_ARG; }
-    if (hough::set_find_lds_limit(f.wg_threads, f.lds_bytes) != hipSuccess) {
-        why = "hipFuncSetAttribute failed for the finder kernel";
-        return HOUGH_ERR_DEVICE;
-    }
     int per_cu = 0;
     if (hough::find_blocks_per_cu(f.wg_threads, f.lds_bytes, &per_cu) != hipSuccess || per_cu < 1) {
         why = "occupancy query failed for the finder kernel";
@@ -328,8 +352,12 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         std::string none;
         Shape f;
         if (make_shape(c, kDenseThreads, 0, lds_max / 2, n_cu, f, none) == HOUGH_OK && f.stream_ok && f.big_ok &&
-            f.max_resident >= 2 * n_cu)
+            f.max_resident >= 2 * n_cu && raise_find_limit(c, f) == hipSuccess)
             c.dense = f;
+    }
+    if (raise_find_limit(c, c) != hipSuccess || (c.wide.max_resident > 0 && raise_find_limit(c, c.wide) != hipSuccess)) {
+        why = "hipFuncSetAttribute failed for the finder kernel";
+        return HOUGH_ERR_DEVICE;
     }
     // |rho| <= r (1 + 2^-24)^3 for r = sqrt(phi^2 + z^2); a rho at least
     // delta inside [rho_min, rho_max] gives a bin in [0, n_rho) after the
@@ -350,7 +378,7 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         } else if (sl + kStaticLds > lds_max) {
             why = "sweep row buffers do not fit in LDS";
             return HOUGH_ERR_INVALID_ARG;
-        } else if (hough::set_sweep_lds_limit(c.sweep_threads, sl) != hipSuccess) {
+        } else if (raise_sweep_limit(c, c.sweep_threads, sl) != hipSuccess) {
             why = "hipFuncSetAttribute failed for the sweep kernel";
             return HOUGH_ERR_DEVICE;
         }
@@ -358,7 +386,7 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     c.single_split = 0;
     if (c.stream_ok && g.sweep_groups == 0 && g.peak_mode != 2) {
         const int sl = hough::sweep_lds_bytes(kSingleSweepThreads, c.pitch);
-        if (sl + kStaticLds <= lds_max && hough::set_sweep_lds_limit(kSingleSweepThreads, sl) == hipSuccess)
+        if (sl + kStaticLds <= lds_max && raise_sweep_limit(c, kSingleSweepThreads, sl) == hipSuccess)
             c.single_split = 1;
     }
     // a few events' large-event first sweeps over one workgroup per finder
@@ -367,22 +395,23 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     if (c.single_split && c.big_ok && g.peak_mode == 1 && g.nms_radius == 1) {
         const int max_hits = 512 + std::min(c.hs_cap & ~63, 56 * 64);
         c.band_lds = hough::band_lds_bytes(c.pitch, max_hits);
-        if (c.band_lds + kStaticLds <= lds_max && hough::set_band_lds_limit(c.band_lds) == hipSuccess)
+        if (c.band_lds + kStaticLds <= lds_max &&
+            raise_lds_limit(c, kLdsBand, 0, c.band_lds, [&] { return hough::set_band_lds_limit(c.band_lds); }) == hipSuccess)
             c.band_split = 1;
     }
     // the time-sliced finder stages a window's hits in the finder's LDS
     // between its calls
     c.tw_lds = c.lds_bytes;
-    if (g.peak_mode != 2 && (hough::set_tw_lds_limit(c.wg_threads, c.tw_lds) != hipSuccess ||
-                             (c.wide.max_resident > 0 &&
-                              hough::set_tw_lds_limit(c.wide.wg_threads, c.wide.lds_bytes) != hipSuccess))) {
+    if (g.peak_mode != 2 &&
+        (raise_tw_limit(c, c.wg_threads, c.tw_lds) != hipSuccess ||
+         (c.wide.max_resident > 0 && raise_tw_limit(c, c.wide.wg_threads, c.wide.lds_bytes) != hipSuccess))) {
         why = "hipFuncSetAttribute failed for the time-sliced finder";
         return HOUGH_ERR_DEVICE;
     }
     int drows = std::min(g.n_theta, std::max(1, (lds_max - kStaticLds) / row_bytes));
     c.dump_rows = std::min(drows, 64);
     c.dump_lds = c.dump_rows * row_bytes;
-    if (hough::set_dump_lds_limit(c.dump_lds) != hipSuccess) {
+    if (raise_lds_limit(c, kLdsDump, 0, c.dump_lds, [&] { return hough::set_dump_lds_limit(c.dump_lds); }) != hipSuccess) {
         why = "hipFuncSetAttribute failed for the dump kernel";
         return HOUGH_ERR_DEVICE;
     }
@@ -393,7 +422,8 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         c.lds_bytes = hough::cf_lds_bytes(c.c_theta * c.c_rho, c.f_theta * c.f_rho, c.wg_threads);
         c.sweep_groups = 0;
         if (c.lds_bytes + kStaticLds > lds_max) { why = "LDS budget exceeded"; return HOUGH_ERR_INVALID_ARG; }
-        if (hough::set_cf_lds_limit(c.wg_threads, c.lds_bytes) != hipSuccess) {
+        if (raise_lds_limit(c, kLdsCf, c.wg_threads, c.lds_bytes,
+                            [&] { return hough::set_cf_lds_limit(c.wg_threads, c.lds_bytes); }) != hipSuccess) {
             why = "hipFuncSetAttribute failed for the coarse-to-fine kernel";
             return HOUGH_ERR_DEVICE;
         }
@@ -406,7 +436,8 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         }
         c.max_resident = per_cu * prop.multiProcessorCount;
         c.tw_lds = std::max(c.lds_bytes, kTwCfLds);
-        if (hough::set_tw_cf_lds_limit(c.wg_threads, c.tw_lds) != hipSuccess) {
+        if (raise_lds_limit(c, kLdsTwCf, c.wg_threads, c.tw_lds,
+                            [&] { return hough::set_tw_cf_lds_limit(c.wg_threads, c.tw_lds); }) != hipSuccess) {
             why = "hipFuncSetAttribute failed for the time-sliced finder";
             return HOUGH_ERR_DEVICE;
         }

@@ -23,9 +23,12 @@ class Library:
             getattr(lib, name).argtypes, getattr(lib, name).restype = real.argtypes, real.restype
         lib.launches.restype = ctypes.c_char_p
         lib.set_memory.argtypes = [ctypes.c_size_t]
+        self.limit = {}   # dynamic LDS that a kernel's launches may ask for, as it was set last
 
     def log(self):
-        return [json.loads(x) for x in self.lib.launches().decode().splitlines()]
+        got = [json.loads(x) for x in self.lib.launches().decode().splitlines()]
+        self.limit.update({(x["limit"], x["threads"]): x["bytes"] for x in got if "limit" in x})
+        return got
 
     def create(self, **cfg):
         c = hough.HoughConfig()
@@ -193,3 +196,26 @@ def test_scratch_limit_of_the_call_without_allocation(host, n_rho, events):
         return lo
     tiled = dict(wg_threads=1024) if n_rho > 1152 else {}
     assert most() >= most(**tiled)
+
+
+def test_a_context_leaves_the_other_contexts_their_lds(host):
+    """The dynamic LDS that a kernel may ask for is one setting per process: making
+    a context never takes from it what another's launches ask for."""
+    configs = [dict(wg_threads=512), dict(), dict(n_rho=2048), dict(wg_threads=512, tile_rows=14), dict(n_rho=512, tile_rows=16),
+               dict(n_theta=180, n_rho=1000, peak_mode=2), dict(n_theta=90, n_rho=500, peak_mode=2), dict(n_rho=3000),
+               dict(n_rho=1000, n_theta=180, peak_mode=ARGMAX), dict(wg_threads=256, tile_rows=6), dict(sweep_groups=2), dict()]
+    live = []
+    for cfg in configs:
+        st, h = host.create(**cfg)
+        assert st == 0
+        host.log()
+        live.append((cfg, h))
+        for c, other in live:
+            for events, hits in ((1, 300), (4, 1200), (300, 9000), (2048, 50000), (2, 9000)):
+                assert host.lib.hough_find(other, None, events, hits, FAKE, FAKE, FAKE, FAKE, hits, FAKE, hits, FAKE) == 0
+                for x in host.log():
+                    kernel = {"find": "find", "picked": "find", "list": "find", "find_cf": "cf"}.get(x.get("launch"))
+                    if kernel:
+                        assert x["lds"] <= host.limit[kernel, x["threads"]], (c, "after", cfg, x, host.limit)
+    for _, h in live:
+        host.lib.hough_destroy(h)
