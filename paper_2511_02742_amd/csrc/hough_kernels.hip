@@ -2895,6 +2895,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                             band_scan_ok<false>(A, kBandHits) && band_ring_ok<NT>(A, kBandHits, 0)
                         ? kBandHits
                         : kChunks * kWave;
+    bool pre = sh.pre == NW;   // k_band swept the first band
     bool big = false;      // large-event path this iteration: peaks in a device-memory slot
     bool big_lds = false;  // the hot set or the peak list outgrew LDS: the event stays large
     int slot = -1;
@@ -2960,7 +2961,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
         // (and the first iteration of an event whose first band k_band swept,
         // or of many hits)
         const bool by_band = !MAX && iter == 0 && n_alive > band_from && n_alive <= kChunks * kWave;
-        big = big_lds || nbatch > 1 || (iter == 0 && sh.pre == NW) || by_band;
+        big = big_lds || nbatch > 1 || (iter == 0 && pre) || by_band;
         // (the LDS-resident hits are read in whole 64-hit chunks, at most
         // 56 of them: the banded sweep flags hot votes in 64 bits)
         if (A.stream_ok && n_alive <= kChunks * kWave + min(A.hs_cap & ~(kWave - 1), 56 * kWave)) {
@@ -3070,7 +3071,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                     __syncthreads();
                     HOUGH_PHASE_MARK(kPhRest);
                     const bool ring = band_ring_ok<NT>(A, n_alive, nx);
-                    if (ring && iter == 0 && sh.pre == NW) {
+                    if (ring && iter == 0 && pre) {
                         // k_band swept this band into the slot (the segment
                         // counts were taken over at the start)
                     } else if (ring) {
@@ -3114,10 +3115,12 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                     }
                 }
             }
-            if (by_band && !done) {
-                // no slot, hits that leave the grid, or more peaks in a band
-                // than its segment holds: as an event of fewer hits
+            if (!MAX && iter == 0 && !done && nbatch == 1 && (by_band || pre)) {
+                // no slot, hits that leave the grid, more peaks in a band than
+                // its segment holds, or a count that order_segments has no place
+                // for: as an event of fewer hits, and without k_band's sweep
                 band_from = kChunks * kWave;
+                pre = false;
                 continue;
             }
         }

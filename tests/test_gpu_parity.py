@@ -890,3 +890,28 @@ def test_large_events_among_others_on_long_rows(gpu_available, kw, list_hits, n_
             assert got[2]["iters"] == want[2]["iters"]
         if n_events >= 70:   # every event by the tiled sweep where the large one outgrows the list, else none of the small
             assert (own.find(*t).to_host()[2]["tiled"] >= n_events) == (n > list_hits)
+
+
+@pytest.mark.parametrize("kw", [{}, {"n_theta": 180, "n_rho": 1000}, {"n_theta": 600, "n_rho": 700}, {"n_rho": 1500}])
+@pytest.mark.parametrize("n_events", [1, 3, 20])
+def test_band_sweep_ahead_that_cannot_be_ordered(gpu_available, kw, n_events):
+    # a few events of 449 to 512 hits, whose first band is swept ahead of the
+    # finder, with a peak of more votes than the ordering of its segments has
+    # counters for (T + 128 and up): the finder then sweeps row by row, as such an
+    # event in a large call does, not tile by tile
+    rng = np.random.default_rng(65)
+    evs = []
+    for i in range(n_events):
+        n, same = (449, 480, 512)[i % 3], (200, 140, 139)[(i + i // 3) % 3]   # equal hits share a bin in every row
+        z, vane = np.full(same, 12.5, np.float32), np.full(same, 3, np.int16)
+        ev = eventgen.pileup_event(65_000 + i, n_tracks=130)
+        z, vane = np.concatenate([z, ev.z[:n - same]]), np.concatenate([vane, ev.vane[:n - same]])
+        order = rng.permutation(n)
+        evs.append((z[order], vane[order]))
+    off = np.concatenate([[0], np.cumsum([len(z) for z, _ in evs])]).astype(np.int64)
+    b = eventgen.Batch(r=np.zeros(off[-1], np.float32), z=np.concatenate([z for z, _ in evs]),
+                       vane=np.concatenate([v for _, v in evs]), offsets=off, events=[])
+    kw = dict(min_votes=12, **kw)
+    got, want = check_batch(b, "a band that cannot be ordered %s" % kw, **kw)
+    assert want.cand["peak_votes"].max() >= 12 + 128
+    assert got[2]["tiled"] == 0, got[2]
