@@ -189,7 +189,7 @@ hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, i
 // The finder on a's events, in a.order, if the first shape was picked (256 or 512 threads).
 hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, hipStream_t s);
 // The finder on list's events, in list.order, if it was not: `groups` workgroups
-// that take one event after the other.
+// of 1024 threads that take one event after the other.
 hipError_t launch_list(const FindArgs &list, Pick *pick, int groups, int wg_threads, int lds_bytes, hipStream_t s);
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s);
 hipError_t launch_dump(const DumpArgs &a, int lds_bytes, hipStream_t s);

@@ -2895,7 +2895,6 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                             band_scan_ok<false>(A, kBandHits) && band_ring_ok<NT>(A, kBandHits, 0)
                         ? kBandHits
                         : kChunks * kWave;
-    bool pre = sh.pre == NW;   // k_band swept the first band
     bool big = false;      // large-event path this iteration: peaks in a device-memory slot
     bool big_lds = false;  // the hot set or the peak list outgrew LDS: the event stays large
     int slot = -1;
@@ -2961,7 +2960,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
         // (and the first iteration of an event whose first band k_band swept,
         // or of many hits)
         const bool by_band = !MAX && iter == 0 && n_alive > band_from && n_alive <= kChunks * kWave;
-        big = big_lds || nbatch > 1 || (iter == 0 && pre) || by_band;
+        big = big_lds || nbatch > 1 || (iter == 0 && sh.pre == NW) || by_band;
         // (the LDS-resident hits are read in whole 64-hit chunks, at most
         // 56 of them: the banded sweep flags hot votes in 64 bits)
         if (A.stream_ok && n_alive <= kChunks * kWave + min(A.hs_cap & ~(kWave - 1), 56 * kWave)) {
@@ -3071,7 +3070,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                     __syncthreads();
                     HOUGH_PHASE_MARK(kPhRest);
                     const bool ring = band_ring_ok<NT>(A, n_alive, nx);
-                    if (ring && iter == 0 && pre) {
+                    if (ring && iter == 0 && sh.pre == NW) {
                         // k_band swept this band into the slot (the segment
                         // counts were taken over at the start)
                     } else if (ring) {
@@ -3115,12 +3114,14 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                     }
                 }
             }
-            if (!MAX && iter == 0 && !done && nbatch == 1 && (by_band || pre)) {
+            if (!MAX && iter == 0 && !done && nbatch == 1 && (by_band || sh.pre == NW)) {
                 // no slot, hits that leave the grid, more peaks in a band than
                 // its segment holds, or a count that order_segments has no place
                 // for: as an event of fewer hits, and without k_band's sweep
                 band_from = kChunks * kWave;
-                pre = false;
+                __syncthreads();
+                if (tid_x() == 0) sh.pre = 0;
+                __syncthreads();
                 continue;
             }
         }
@@ -3235,8 +3236,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 // The event finder as a call: inlined into the window loop below, the values
 // that the compiler keeps over the loop took 1136 B of scratch a lane; the call
 // saves and restores 20 registers instead. *A is read with scalar loads, like a
-// kernel's arguments (vector loads held in registers: 480 B).
-template <int NT, bool MAX>
+// kernel's arguments (vector loads held in registers: 480 B). WHO: a copy for each
+// kernel that calls it (one copy for both saved 208 B instead of 112).
+template <int NT, bool MAX, int WHO>
 __device__ __noinline__ void find_event_call(const FindArgs *A, int e, int64_t b, int64_t n) {
     __shared__ Shared sh;
     const FindArgs &a = tw::const_args(A);
@@ -3260,8 +3262,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 // first, by as many workgroups as are resident at once (k_find with a workgroup per
 // event in its place cost a call that takes the dense shape 10 us at 4096 events,
 // this 3; where it runs, its event function being a call, it takes 1 to 4 % longer).
-template <int NT, bool MAX>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_list(Pick *P) {
+constexpr int kListThreads = 1024;
+template <bool MAX>
+__global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_list(Pick *P) {
     if (P->first != 0) return;
     __shared__ int at;
     const FindArgs &A = tw::const_args(&P->list);
@@ -3273,7 +3276,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         if (i >= A.n_events) return;
         const int e = __builtin_amdgcn_readfirstlane(A.order[i]);
         const int64_t b = uniform64(A.offsets[e]);
-        find_event_call<NT, MAX>(&P->list, e, b, uniform64(A.offsets[e + 1]) - b);
+        find_event_call<kListThreads, MAX, 1>(&P->list, e, b, uniform64(A.offsets[e + 1]) - b);
         __syncthreads();
     }
 }
@@ -3286,7 +3289,7 @@ template <int NT, bool MAX>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_tw_run(TwArgs W) {
     __shared__ tw::Shared T;
     tw::run<NT>(W, tw::const_args(W.find), g_lds, T,
-                [&](int e, int64_t b, int64_t n) { find_event_call<NT, MAX>(W.find, e, b, n); });
+                [&](int e, int64_t b, int64_t n) { find_event_call<NT, MAX, 0>(W.find, e, b, n); });
 }
 
 // First histogram sweep of each event split over `groups` workgroups: group g
@@ -3855,13 +3858,13 @@ hipError_t set_find_lds_limit(int wg_threads, int lds_bytes) {
                 const hipError_t e = lds_limit(f, lds_bytes);
                 if (e != hipSuccess) return e;
             }
-        for (const void *f : {reinterpret_cast<const void *>(k_find<nt()>), reinterpret_cast<const void *>(k_argmax<nt()>),
-                              reinterpret_cast<const void *>(k_list<nt(), false>),
-                              reinterpret_cast<const void *>(k_list<nt(), true>)}) {
-            const hipError_t e = lds_limit(f, lds_bytes);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        if constexpr (nt() == kListThreads)
+            for (const void *f : {reinterpret_cast<const void *>(k_list<false>), reinterpret_cast<const void *>(k_list<true>)}) {
+                const hipError_t e = lds_limit(f, lds_bytes);
+                if (e != hipSuccess) return e;
+            }
+        const hipError_t e = lds_limit(reinterpret_cast<const void *>(k_find<nt()>), lds_bytes);
+        return e != hipSuccess ? e : lds_limit(reinterpret_cast<const void *>(k_argmax<nt()>), lds_bytes);
     });
 }
 
@@ -3912,13 +3915,12 @@ hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, hipSt
 }
 
 hipError_t launch_list(const FindArgs &list, Pick *pick, int groups, int wg_threads, int lds_bytes, hipStream_t s) {
-    return with_threads(wg_threads, [&](auto nt) {
-        if (list.peak_mode == 0)
-            hipLaunchKernelGGL((k_list<nt(), true>), dim3(groups), dim3(nt()), lds_bytes, s, pick);
-        else
-            hipLaunchKernelGGL((k_list<nt(), false>), dim3(groups), dim3(nt()), lds_bytes, s, pick);
-        return hipGetLastError();
-    });
+    if (wg_threads != kListThreads) return hipErrorInvalidValue;
+    if (list.peak_mode == 0)
+        hipLaunchKernelGGL(k_list<true>, dim3(groups), dim3(kListThreads), lds_bytes, s, pick);
+    else
+        hipLaunchKernelGGL(k_list<false>, dim3(groups), dim3(kListThreads), lds_bytes, s, pick);
+    return hipGetLastError();
 }
 
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s) {

@@ -58,3 +58,20 @@ def test_a_returned_slot_is_written_back_whole(kernels, kind):
             wait = max(k for k in range(bar) if STORES_IN.match(lines[k]))
             assert bar - wait <= 8 and not any(VMEM.match(x) for x in lines[wait:bar]), (name, lines[bar - 8:bar + 1])
     assert seen >= 9   # three ways out of an event, three workgroup sizes
+
+
+def _remark(remarks, kind, what):
+    return {n: int(re.search(what + r": (\d+)", blk).group(1)) for n, blk in remarks.items() if kind in n}
+
+
+def test_finder_kernels_keep_no_scratch(kernels):
+    """The largest-bin search and the first of two shapes, like the finder, keep
+    their working set in registers and LDS; where the event function is a call (the
+    time-sliced finder, the list of events) it saves some 20 to 50 registers."""
+    _, remarks = kernels
+    for kind, sizes in (("k_argmax", 3), ("k_picked", 4)):
+        scratch = _remark(remarks, kind, r"ScratchSize \[bytes/lane\]")
+        assert len(scratch) == sizes and set(scratch.values()) == {0}, scratch
+    for kind, sizes in (("k_tw_run", 6), ("k_list", 2)):
+        scratch = _remark(remarks, kind, r"ScratchSize \[bytes/lane\]")
+        assert len(scratch) == sizes and max(scratch.values()) <= 192, scratch
