@@ -280,12 +280,13 @@ hough_status make_shape(const Ctx &c, int threads, int tile_rows, int lds_max, i
     f.tile_bytes = (f.tile_bytes + 15) & ~15;
     f.lds_bytes = f.tile_bytes + hough::find_lds_extra(f.wg_threads, kHotCap, kPeakKeep);
     if (f.lds_bytes + kStaticLds > lds_max) { why = "LDS budget exceeded"; return HOUGH_ERR_INVALID_ARG; }
-    int per_cu = 0;
-    if (hough::find_blocks_per_cu(f.wg_threads, f.lds_bytes, &per_cu) != hipSuccess || per_cu < 1) {
+    int per_cu = 0, most = 0;
+    if (hough::find_blocks_per_cu(f.wg_threads, g.peak_mode == 0, f.lds_bytes, &per_cu, &most) != hipSuccess || per_cu < 1) {
         why = "occupancy query failed for the finder kernel";
         return HOUGH_ERR_DEVICE;
     }
     f.max_resident = per_cu * n_cu;
+    f.slots = most * n_cu;
     // row-stream layout inside the tile: one row buffer per wave (reused by
     // the hash table of the window test: a power-of-two slot count of 8 B,
     // at most half full), then the hot set, then the sorted peak keys
@@ -435,6 +436,7 @@ hough_status choose_shape(Ctx &c, std::string &why) {
             return HOUGH_ERR_DEVICE;
         }
         c.max_resident = per_cu * prop.multiProcessorCount;
+        c.slots = c.max_resident;
         c.tw_lds = std::max(c.lds_bytes, kTwCfLds);
         if (raise_lds_limit(c, kLdsTwCf, c.wg_threads, c.tw_lds,
                             [&] { return hough::set_tw_cf_lds_limit(c.wg_threads, c.tw_lds); }) != hipSuccess) {
@@ -500,7 +502,7 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
     const size_t o_ghs = ghs_events > 0 ? take(8 * (size_t)ghs_events * (size_t)std::max(c.hs_cap, 1)) : 0;
     // large-event slots: no more workgroups than events, nor than fit the
     // device at once, hold one at a time
-    const int resident = dense ? std::max(c.max_resident, c.dense.max_resident) : c.max_resident;
+    const int resident = dense ? std::max(c.slots, c.dense.slots) : c.slots;
     const int32_t slots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(ne, std::max(resident, 1)));
     const int64_t slot_bytes = (int64_t)align256(8 * 2 * (size_t)big_pk);
     const size_t o_pflags = take(4 * ((size_t)slots + 2 * kBandCall));

@@ -195,8 +195,9 @@ hipError_t launch_compact(const CompactArgs &a, hipStream_t s);
 hipError_t launch_dump(const DumpArgs &a, int lds_bytes, hipStream_t s);
 hipError_t launch_set_offsets(int64_t *offsets, int64_t n, hipStream_t s);
 hipError_t set_find_lds_limit(int wg_threads, int lds_bytes);
-// Finder workgroups one CU holds at once for this shape.
-hipError_t find_blocks_per_cu(int wg_threads, int lds_bytes, int *blocks);
+// Finder workgroups one CU holds at once for this shape, and the most that it holds
+// of any kernel that takes large-event slots (the time-sliced finder among them).
+hipError_t find_blocks_per_cu(int wg_threads, bool argmax, int lds_bytes, int *blocks, int *most);
 // LDS bytes of k_find beyond the tile (hot list, peak lists, dummies).
 int find_lds_extra(int wg_threads, int hcap, int pkeep);
 hipError_t set_dump_lds_limit(int lds_bytes);

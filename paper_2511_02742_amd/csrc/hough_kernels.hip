@@ -3816,19 +3816,6 @@ hipError_t launch_set_offsets(int64_t *offsets, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t find_blocks_per_cu(int wg_threads, int lds_bytes, int *blocks) {
-    switch (wg_threads) {
-    case 256:
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_find<256>, 256, lds_bytes);
-    case 512:
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_find<512>, 512, lds_bytes);
-    case 1024:
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_find<1024>, 1024, lds_bytes);
-    default:
-        return hipErrorInvalidValue;
-    }
-}
-
 namespace {
 // f(std::integral_constant<int, NT>) for the workgroup sizes there are.
 template <typename F>
@@ -3849,6 +3836,25 @@ hipError_t lds_limit(const void *f, int lds_bytes) {
     return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
 }
 }  // namespace
+
+hipError_t find_blocks_per_cu(int wg_threads, bool argmax, int lds_bytes, int *blocks, int *most) {
+    return with_threads(wg_threads, [&](auto nt) {
+        auto query = [&](auto kernel, int *n) {
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, kernel, nt(), lds_bytes);
+        };
+        hipError_t e = argmax ? query(k_argmax<nt()>, blocks) : query(k_find<nt()>, blocks);
+        *most = *blocks;
+        auto more = [&](auto kernel) {
+            int n = 0;
+            if (e == hipSuccess) e = query(kernel, &n);
+            *most = std::max(*most, n);
+        };
+        if constexpr (nt() < 1024) argmax ? more(k_picked<nt(), true>) : more(k_picked<nt(), false>);
+        if constexpr (nt() == kListThreads) argmax ? more(k_list<true>) : more(k_list<false>);
+        argmax ? more(k_tw_run<nt(), true>) : more(k_tw_run<nt(), false>);
+        return e;
+    });
+}
 
 hipError_t set_find_lds_limit(int wg_threads, int lds_bytes) {
     return with_threads(wg_threads, [&](auto nt) {

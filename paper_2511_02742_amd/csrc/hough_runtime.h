@@ -55,6 +55,7 @@ struct Shape {
     int big_sort = 0;                         // longest equal-count run sorted in LDS
     int big_ok = 0, roll_off = 0, roll_bytes = 0;  // banded large-event sweep
     int max_resident = 0;                     // finder workgroups resident at once on the device
+    int slots = 0;                            // the most of any kernel that takes large-event slots
 };
 
 // The context's own shape is the configuration's, or the default.

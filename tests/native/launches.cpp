@@ -69,11 +69,15 @@ hipError_t set_dump_lds_limit(int bytes) {
     note("{\"limit\": \"dump\", \"threads\": 0, \"bytes\": %d}", bytes);
     return hipSuccess;
 }
-hipError_t find_blocks_per_cu(int threads, int lds, int *blocks) {   // four waves per SIMD, 160 KB
+hipError_t cf_blocks_per_cu(int threads, int lds, int *blocks) {   // four waves per SIMD, 160 KB
     *blocks = std::min(1024 / threads, (160 << 10) / (lds + kStaticLds));
     return hipSuccess;
 }
-hipError_t cf_blocks_per_cu(int threads, int lds, int *blocks) { return find_blocks_per_cu(threads, lds, blocks); }
+hipError_t find_blocks_per_cu(int threads, bool argmax, int lds, int *blocks, int *most) {
+    cf_blocks_per_cu(threads, lds, blocks);
+    *most = threads == 256 && argmax ? *blocks + 1 : *blocks;   // some kernel with fewer registers
+    return hipSuccess;
+}
 
 hipError_t launch_find(const FindArgs &a, int threads, int lds, hipStream_t) {
     note("{\"launch\": \"find\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"stream_ok\": %d, \"hs_cap\": %d, \"events\": %d, "

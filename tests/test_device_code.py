@@ -75,3 +75,12 @@ def test_finder_kernels_keep_no_scratch(kernels):
     for kind, sizes in (("k_tw_run", 6), ("k_list", 2)):
         scratch = _remark(remarks, kind, r"ScratchSize \[bytes/lane\]")
         assert len(scratch) == sizes and max(scratch.values()) <= 192, scratch
+
+
+def test_finder_kernels_share_a_cu_alike(kernels):
+    """Every kernel that takes large-event slots runs four waves per SIMD (at most
+    128 registers), so none has more workgroups resident than another."""
+    _, remarks = kernels
+    for kind in ("k_find", "k_argmax", "k_picked", "k_list", "k_tw_run"):
+        waves = _remark(remarks, kind, r"Occupancy \[waves/SIMD\]")
+        assert len(waves) >= 2 and set(waves.values()) == {4}, waves

@@ -219,3 +219,13 @@ def test_a_context_leaves_the_other_contexts_their_lds(host):
                         assert x["lds"] <= host.limit[kernel, x["threads"]], (c, "after", cfg, x, host.limit)
     for _, h in live:
         host.lib.hough_destroy(h)
+
+
+@pytest.mark.parametrize("cfg,slots", [({"wg_threads": 256, "tile_rows": 6}, 768), ({"wg_threads": 256, "tile_rows": 6, "peak_mode": ARGMAX}, 1024),
+                                       ({"wg_threads": 256, "peak_mode": ARGMAX}, 512), ({}, 512)])
+def test_a_slot_for_every_workgroup(host, cfg, slots):
+    """As many large-event slots as the most workgroups that any kernel taking them
+    has resident at once (here one more per CU than the finder, for 256 threads of
+    the largest-bin search)."""
+    find = [x for x in host.calls(4096, 4096 * 400, n_rho=1000, **cfg) if x["launch"] in ("find", "picked")][0]
+    assert find["slots"] == slots
