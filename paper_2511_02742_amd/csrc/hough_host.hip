@@ -222,8 +222,9 @@ void build_tables(Ctx &c) {
 }
 
 // The dynamic LDS that a kernel's launches may ask for is one setting of the process
-// per device, which every context's shapes share: it is only ever raised, by the
-// shapes that a context takes.
+// per device, which every context's shapes share: the shapes that a context takes
+// set it to the most that any has asked for (again each time: a reset of the device
+// forgets it).
 enum LdsKernel { kLdsFind, kLdsTw, kLdsCf, kLdsTwCf, kLdsSweep, kLdsBand, kLdsDump };
 template <class Set>
 hipError_t raise_lds_limit(const Ctx &c, LdsKernel kernel, int threads, int bytes, Set set) {
@@ -231,20 +232,19 @@ hipError_t raise_lds_limit(const Ctx &c, LdsKernel kernel, int threads, int byte
     static std::map<std::tuple<int, int, int>, int> limit;
     std::lock_guard<std::mutex> g(mu);
     int &now = limit[{c.device, (int)kernel, threads}];
-    if (bytes <= now) return hipSuccess;
-    const hipError_t e = set();
-    if (e == hipSuccess) now = bytes;
+    const hipError_t e = set(std::max(bytes, now));
+    if (e == hipSuccess) now = std::max(bytes, now);
     return e;
 }
 hipError_t raise_find_limit(const Ctx &c, const Shape &f) {
     return raise_lds_limit(c, kLdsFind, f.wg_threads, f.lds_bytes,
-                           [&] { return hough::set_find_lds_limit(f.wg_threads, f.lds_bytes); });
+                           [&](int most) { return hough::set_find_lds_limit(f.wg_threads, most); });
 }
 hipError_t raise_tw_limit(const Ctx &c, int threads, int bytes) {
-    return raise_lds_limit(c, kLdsTw, threads, bytes, [&] { return hough::set_tw_lds_limit(threads, bytes); });
+    return raise_lds_limit(c, kLdsTw, threads, bytes, [&](int most) { return hough::set_tw_lds_limit(threads, most); });
 }
 hipError_t raise_sweep_limit(const Ctx &c, int threads, int bytes) {
-    return raise_lds_limit(c, kLdsSweep, threads, bytes, [&] { return hough::set_sweep_lds_limit(threads, bytes); });
+    return raise_lds_limit(c, kLdsSweep, threads, bytes, [&](int most) { return hough::set_sweep_lds_limit(threads, most); });
 }
 
 // The shape of `threads` per workgroup with LDS tiles of tile_rows own rows (0:
@@ -397,7 +397,7 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         const int max_hits = 512 + std::min(c.hs_cap & ~63, 56 * 64);
         c.band_lds = hough::band_lds_bytes(c.pitch, max_hits);
         if (c.band_lds + kStaticLds <= lds_max &&
-            raise_lds_limit(c, kLdsBand, 0, c.band_lds, [&] { return hough::set_band_lds_limit(c.band_lds); }) == hipSuccess)
+            raise_lds_limit(c, kLdsBand, 0, c.band_lds, hough::set_band_lds_limit) == hipSuccess)
             c.band_split = 1;
     }
     // the time-sliced finder stages a window's hits in the finder's LDS
@@ -412,7 +412,7 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     int drows = std::min(g.n_theta, std::max(1, (lds_max - kStaticLds) / row_bytes));
     c.dump_rows = std::min(drows, 64);
     c.dump_lds = c.dump_rows * row_bytes;
-    if (raise_lds_limit(c, kLdsDump, 0, c.dump_lds, [&] { return hough::set_dump_lds_limit(c.dump_lds); }) != hipSuccess) {
+    if (raise_lds_limit(c, kLdsDump, 0, c.dump_lds, hough::set_dump_lds_limit) != hipSuccess) {
         why = "hipFuncSetAttribute failed for the dump kernel";
         return HOUGH_ERR_DEVICE;
     }
@@ -424,7 +424,7 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         c.sweep_groups = 0;
         if (c.lds_bytes + kStaticLds > lds_max) { why = "LDS budget exceeded"; return HOUGH_ERR_INVALID_ARG; }
         if (raise_lds_limit(c, kLdsCf, c.wg_threads, c.lds_bytes,
-                            [&] { return hough::set_cf_lds_limit(c.wg_threads, c.lds_bytes); }) != hipSuccess) {
+                            [&](int most) { return hough::set_cf_lds_limit(c.wg_threads, most); }) != hipSuccess) {
             why = "hipFuncSetAttribute failed for the coarse-to-fine kernel";
             return HOUGH_ERR_DEVICE;
         }
@@ -439,7 +439,7 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         c.slots = c.max_resident;
         c.tw_lds = std::max(c.lds_bytes, kTwCfLds);
         if (raise_lds_limit(c, kLdsTwCf, c.wg_threads, c.tw_lds,
-                            [&] { return hough::set_tw_cf_lds_limit(c.wg_threads, c.tw_lds); }) != hipSuccess) {
+                            [&](int most) { return hough::set_tw_cf_lds_limit(c.wg_threads, most); }) != hipSuccess) {
             why = "hipFuncSetAttribute failed for the time-sliced finder";
             return HOUGH_ERR_DEVICE;
         }
