@@ -223,6 +223,11 @@ hough_status hough_output_bounds(const hough_ctx *ctx, int32_t n_events, int64_t
  * Returns HOUGH_ERR_INVALID_ARG for null pointers, negative sizes or a bad
  * context, HOUGH_ERR_OOM if the workspace cannot grow, HOUGH_ERR_DEVICE if a
  * launch fails.
+ * The workspace takes about 27 B per hit, 112 B per event and 512 KiB per
+ * large-event slot, one for each finder workgroup resident at once (128 MiB for
+ * the default shape) but no more than events. For calls of 768 events and more
+ * with no shape configured it holds twice the slots (256 MiB); where that
+ * allocation fails such calls keep the default shape and its slots.
  */
 hough_status hough_find(hough_ctx *ctx, void *stream, int32_t n_events, int64_t n_hits_total,
                         const int64_t *event_offsets, const float *z, const int16_t *vane,
@@ -274,7 +279,12 @@ hough_status hough_debug_accumulator(hough_ctx *ctx, void *stream, int64_t n_hit
 hough_status hough_tables(const hough_ctx *ctx, float *cos_t, float *sin_t, float *phi_v,
                           float *inv_w, float *theta_c, float *rho_c);
 
-/* Launch shape chosen for this context (after defaults/tuning). */
+/* The context's own launch shape (after defaults/tuning). With no shape
+ * configured (wg_threads, tile_rows and sweep_groups 0) two kinds of hough_find
+ * calls may run another, with the same outputs: calls of 768 events and more
+ * one of two workgroups per compute unit, unless an event dwarfs the others;
+ * calls on rows of more than 1152 bins one of 1024 threads, if an event
+ * outgrows the own shape's lists (2560 hits or more). */
 hough_status hough_launch_shape(const hough_ctx *ctx, int32_t *tile_rows, int32_t *wg_threads,
                                 int32_t *lds_bytes);
 
@@ -507,6 +517,8 @@ hough_status hough_server_get_stats(const hough_server *server, hough_server_sta
  * HOUGH_ERR_INVALID_ARG (bad pointers, sizes or tw configuration, n_vanes
  * outside 3..1024), HOUGH_ERR_CAPACITY (outputs too small), HOUGH_ERR_OOM.
  * The context's workspace grows on demand (hipMalloc) as for hough_find.
+ * One workgroup takes a timeline through all its windows: the finder's launch
+ * shape applies to it, sweep_groups and sweep_threads do not.
  */
 typedef struct {
     float window_ns;        /* window width (10)                                   */

@@ -87,13 +87,25 @@ constexpr int kSmallCall = 8;
 //   275 hits           245 / 266      319 / 266    398 / 307    1458 / 1031
 //   550 hits           555 / 531      800 / 714    1053 / 917   3870 / 3202
 //   1 to 150 tracks                   570 / 575    727 / 632    2848 / 2234
-// and alike on 180 rows (550 hits at 1024 events 638 / 474). Below kDenseRho rho
-// bins more bins reach T than its hot set holds (512 x 512 bins, 139 hits:
-// 216 / 236 at 1024 events, 726 / 469 at 4096), and so on more than kDenseRows rows
-// (9000, 56 hits: 939 / 1409 at 1024). The largest bin alone goes peak after peak on
-// the hot set, and one that does not fit costs a sweep per peak: only events
-// of few hits and votes take the shape (1024 events of 275 hits on 180 rows
-// 237 / 146, on 1024 rows 450 / 2401).
+// and alike on 180 rows (550 hits at 1024 events 638 / 474). On fewer rho bins than
+// kDenseRho more bins reach T than its hot set holds, and calls of few workgroups
+// lose, from the fewest events on that any rows do; on 180 rows none does yet. Past
+// kDenseRows the row's sweep outweighs what overlaps with it, somewhere between
+// 2048 and 4096 rows. Both lines lie on the safe side of what was measured:
+//   27 hits, 110, 275        1024 events                              4096 events
+//   180 rows, 600 bins       96 / 62     144 / 92     258 / 184       318 / 174   482 / 271   922 / 610
+//   180 rows, 900 bins       92 / 59     135 / 86     214 / 146       303 / 165   465 / 259   759 / 453
+//   1024 rows, 600 bins      130 / 93    219 / 293    681 / 769       448 / 283   752 / 527   2517 / 2457
+//   1024 rows, 768 bins      127 / 91    202 / 233    479 / 634       438 / 278   721 / 477   1803 / 1731
+//   1024 rows, 900 bins      125 / 91    199 / 153    416 / 501       432 / 275   707 / 464   1557 / 1355
+//   1500 rows, 1024 bins     142 / 107   230 / 179    484 / 408       493 / 329   825 / 564   1829 / 1386
+//   2048 rows, 1024 bins     160 / 127   271 / 223    613 / 603       567 / 396
+//   4096 rows, 1024 bins     235 / 203   436 / 715    1198 / 1923     845 / 641
+// The largest bin alone goes peak after peak on the hot set, and one that does
+// not fit costs a sweep per peak: only events of few hits and votes take the shape
+// (1024 events of 275 hits on 180 rows 237 / 146, on 1024 rows 450 / 2401). The same
+// line holds for local maxima below kDenseAny events; it leaves out 275 hits at 768
+// events on 1024 rows, which gain (above), and keeps 512 events, which lose, away.
 // The host knows the events' number and mean size, not the largest, and a few
 // events that dwarf the rest end their call later in it (1 % of 200 tracks among 768
 // of 10 on 180 rows 486 / 613), or outgrow its shorter lists and are swept tile by
@@ -118,7 +130,10 @@ constexpr int64_t kRegisterHits = 512;    // alive hits the finder holds in regi
 // k_band also takes events of fewer hits than the register batch, from this
 // many on: about where a pileup event's window-test peaks outgrow the
 // finder's LDS peak list (1024 entries), which sends it to the large-event
-// path after a wasted row-stream sweep
+// path after a wasted row-stream sweep. The split sweep / k_band (us): 352 hits alone 66 /
+// 84, 8 of them 144 / 114, 64 of them 143 / 198; 400 hits 98 / 91, 201 / 120, 171 /
+// 210; 448 hits 130 / 100, 381 / 134, 189 / 225. A line by the call's events would
+// lie at 400 hits for up to 8 and past 448 for 64.
 constexpr int64_t kBandMinHits = 448;
 }  // namespace
 thread_local std::string g_last_global_error;
@@ -468,9 +483,13 @@ int64_t list_hits(const Shape &f) { return kRegisterHits + std::min(f.hs_cap & ~
 //   2.7    4096, 1 % of 200 tracks among 10            644 / 873
 //   3.9    2048, 1 % of 60 tracks among 5              237 / 245
 //   7.4    768, 1 % of 100 tracks among 10             269 / 356
-// and with no event of more than kDenseCalm hits
+// with no event of more than kDenseCalm hits
 //   2.6    2048, 1 % of 40 tracks among 5              226 / 151
 //   6.0    768, 1 % of 40 tracks among 5               102 / 101 (180 rows 73 / 58)
+// and with none of more than 512 on 180 rows
+//   8.6    768, 1 % of 60 tracks among 5               78 / 86 (99 by k_list)
+// The largest bin alone (180 rows) loses little by a large event that fits the list
+// (768, 1 % of 200 tracks among 10: 1925 / 2051, of 100: 422 / 429).
 int64_t dense_hits(const Ctx &c, int64_t n_hits) {
     const int64_t list = list_hits(c.dense);
     if (c.cfg.peak_mode == 0) return list;
