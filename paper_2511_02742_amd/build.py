@@ -9,6 +9,8 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -26,7 +28,6 @@ HIPCC_FLAGS = [
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     # the bin index must be the same rounded float expression as on the host
     "-ffp-contract=off",
     # no packed fp32 instructions in device code
@@ -44,14 +45,22 @@ def hipcc() -> str:
 
 
 def build_library(verbose: bool = False, phase_clocks: bool = False) -> str:
-    """Compiles the library (always) and returns its path."""
+    """Compiles the library (always), one source per process, and returns its path."""
     out = LIB_PHASES if phase_clocks else LIB
     tmp = out + ".tmp%d" % os.getpid()
-    cmd = [hipcc()] + HIPCC_FLAGS + (["-DHOUGH_PHASE_CLOCKS"] if phase_clocks else []) + \
-        ["-I", INCLUDE, "-I", CSRC, "-o", tmp] + SOURCES
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    flags = HIPCC_FLAGS + (["-DHOUGH_PHASE_CLOCKS"] if phase_clocks else [])
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
+
+    with tempfile.TemporaryDirectory() as d:
+        objects = [os.path.join(d, os.path.basename(s) + ".o") for s in SOURCES]
+        with ThreadPoolExecutor(len(SOURCES)) as pool:
+            list(pool.map(lambda so: run([hipcc()] + flags + ["-I", INCLUDE, "-I", CSRC, "-c", so[0], "-o", so[1]]),
+                          zip(SOURCES, objects)))
+        run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objects)
     os.replace(tmp, out)
     return out
 
