@@ -961,7 +961,7 @@ def coarse_fine_bench(args, batch, z, vane, offs, log, lds_vote_peak=None, refs=
         kavg = kern_ms / max(launches, 1)
         res[name] = {"events_per_s": round(N_EVENTS * args.steps / wall, 1),
                      "ms_per_step": round(1e3 * wall / args.steps, 4), "kernel_avg_ms": round(kavg, 4),
-                     "kernel": "k_find_cf" if name == "coarse_fine" else "k_find",
+                     "kernel": "k_find_cf" if name == "coarse_fine" else "k_picked",   # (4096 even events: the shape of two per CU)
                      "evals": info["evals"], "evals_per_s": round(info["evals"] / (kavg * 1e-3), 1),
                      "votes": info["votes"],
                      "lds_frac_vote_pattern": round(info["votes"] / (kavg * 1e-3) / lds_vote_peak, 4)
