@@ -350,9 +350,10 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     const int row_bytes = 4 * c.pitch;
     hough_status st = make_shape(c, g.wg_threads > 0 ? g.wg_threads : 1024, g.tile_rows, lds_max, n_cu, c, why);
     if (st) return st;
-    // rows too long for sixteen waves' buffers and a hot set: as many waves as
-    // have room for both, or every event would take the tiled path (768 events of
-    // 272 hits on 2048 x 2048 bins: 2328 -> 425 us)
+    // rows too long for sixteen waves' buffers and a hot set, or too few of them
+    // for a tile that holds those: as many waves as have room for both, or every
+    // event would take the tiled path (768 events of 272 hits on 2048 x 2048 bins:
+    // 2328 -> 425 us)
     const bool long_rows = !c.stream_ok;
     for (int t = 512; t >= 256 && g.wg_threads == 0 && g.tile_rows == 0 && g.peak_mode != 2 && !c.stream_ok; t /= 2) {
         std::string none;
@@ -364,7 +365,8 @@ hough_status choose_shape(Ctx &c, std::string &why) {
             static_cast<Shape &>(c) = f;
         }
     }
-    if (g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2) {
+    // (beside sixteen waves: they are what its calls fall back to)
+    if (g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2 && c.wide.max_resident == 0) {
         std::string none;
         Shape f;
         if (make_shape(c, kDenseThreads, 0, lds_max / 2, n_cu, f, none) == HOUGH_OK && f.stream_ok && f.big_ok &&

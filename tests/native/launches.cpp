@@ -108,12 +108,12 @@ hipError_t launch_order_pick(const FindArgs &a, int32_t *, Pick *, int64_t hits,
 hipError_t launch_picked(const FindArgs &a, int threads, int lds, hipStream_t) {
     note("{\"launch\": \"picked\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"hs_cap\": %d, \"events\": %d, \"slots\": %d}", threads,
          lds, a.tile_rows, a.hs_cap, a.n_events, a.pool_slots);
-    return hipSuccess;
+    return threads == 512 || threads == 256 ? hipSuccess : 1;
 }
 hipError_t launch_list(const FindArgs &a, Pick *, int groups, int threads, int lds, hipStream_t) {
     note("{\"launch\": \"list\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"groups\": %d, \"stream_ok\": %d, \"split\": %d}", threads, lds,
          a.tile_rows, groups, a.stream_ok, a.g_hs != nullptr);
-    return hipSuccess;
+    return threads == 1024 ? hipSuccess : 1;   // the kernels there are
 }
 hipError_t launch_compact(const CompactArgs &a, hipStream_t) {
     note("{\"launch\": \"compact\", \"ordered\": %d}", a.ordered);

@@ -915,3 +915,22 @@ def test_band_sweep_ahead_that_cannot_be_ordered(gpu_available, kw, n_events):
     got, want = check_batch(b, "a band that cannot be ordered %s" % kw, **kw)
     assert want.cand["peak_votes"].max() >= 12 + 128
     assert got[2]["tiled"] == 0, got[2]
+
+
+@pytest.mark.parametrize("n_theta,n_rho", [(1, 1024), (7, 1025), (13, 1000), (14, 1024), (16, 1152)])
+@pytest.mark.parametrize("peak_mode", [0, 1])
+def test_many_events_on_few_rows(gpu_available, n_theta, n_rho, peak_mode):
+    # too few rows for a tile that holds sixteen waves' buffers and a hot set: the
+    # own shape has fewer waves, and calls of many events have no shape of two per CU
+    import torch
+    kw = dict(n_theta=n_theta, n_rho=n_rho, peak_mode=peak_mode, min_votes=4)
+    pool = [eventgen.pileup_event(66_000 + i, n_tracks=n) for i, n in enumerate((3, 8, 20, 1, 12))] + [eventgen.pileup_event(66_100, n_tracks=300)]
+    own, one = finder(**kw), finder(wg_threads=1024, **kw)
+    dev = torch.device("cuda", 0)
+    for n_events, last in ((768, 5), (1100, 5), (1100, 6)):
+        evs = [pool[i % 5] for i in range(n_events - 1)] + [pool[last - 1]]
+        b = eventgen.make_batch(evs)
+        t = [torch.from_numpy(x).to(dev) for x in (b.z, b.vane, b.offsets)]
+        got, want = own.find(*t).to_host(), one.find(*t).to_host()
+        assert got[2]["status"] == want[2]["status"] == 0 and got[2]["candidates"] == want[2]["candidates"]
+        assert got[0].tobytes() == want[0].tobytes() and np.array_equal(got[1], want[1]) and got[2]["iters"] == want[2]["iters"]

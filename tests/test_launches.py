@@ -229,3 +229,27 @@ def test_a_slot_for_every_workgroup(host, cfg, slots):
     the largest-bin search)."""
     find = [x for x in host.calls(4096, 4096 * 400, n_rho=1000, **cfg) if x["launch"] in ("find", "picked")][0]
     assert find["slots"] == slots
+
+
+@pytest.mark.parametrize("n_theta", [1, 2, 5, 7, 8, 13, 14, 15, 16, 30, 64, 180, 1024, 1025])
+@pytest.mark.parametrize("mode", [NMS, ARGMAX])
+def test_every_grid_has_its_launches(host, n_theta, mode):
+    """Over grids from one row to many, of short rows to the longest: no call is
+    enqueued with a shape that no kernel has, nor with more LDS than there is."""
+    for n_rho in (5, 64, 500, 512, 900, 999, 1000, 1024, 1025, 1152, 1153, 1500, 2048, 2304, 2305, 3000, 4096, 4704, 4705, 9000):
+        for extra in ({}, {"nms_radius": 2}, {"wg_threads": 256}, {"wg_threads": 512}, {"sweep_groups": 2, "sweep_threads": 512}):
+            cfg = dict(n_theta=n_theta, n_rho=n_rho, peak_mode=mode, rho_min=-750.0, rho_max=750.0, **extra)
+            st, h = host.create(**cfg)
+            if st != 0:   # rows that no LDS tile holds, by the configured threads or a wide window
+                assert n_rho >= 4096
+                continue
+            host.log()
+            for events, hits in ((1, 55), (1, 5000), (2, 300), (9, 9000), (64, 9000), (300, 30000), (768, 20000), (1100, 60000),
+                                 (4096, 100000), (4096, 2000000)):
+                for fn in (host.lib.hough_find, host.lib.hough_find_noalloc):
+                    r = fn(h, None, events, hits, FAKE, FAKE, FAKE, FAKE, hits, FAKE, hits, FAKE)
+                    assert r in (0, -2 if fn is host.lib.hough_find_noalloc else 0), (cfg, events, hits, r)
+                    for x in host.log():
+                        if x.get("launch") in ("find", "picked", "list"):
+                            assert x["lds"] + 2048 <= 160 << 10 and x["threads"] in (256, 512, 1024)
+            host.lib.hough_destroy(h)
