@@ -282,10 +282,9 @@ hough_status hough_tables(const hough_ctx *ctx, float *cos_t, float *sin_t, floa
 /* The context's own launch shape (after defaults/tuning). With no shape
  * configured (wg_threads, tile_rows and sweep_groups 0) two kinds of hough_find
  * calls may run another, with the same outputs: calls of 768 events and more
- * one of two workgroups per compute unit, unless an event dwarfs the others;
- * calls on grids where the own one has fewer than 1024 threads (rows of more
- * than 1152 bins, or too few of them) one of 1024, if an event outgrows the
- * own one's lists. */
+ * one of two workgroups per compute unit, unless an event dwarfs the others; and
+ * where the own one has fewer than 1024 threads (rows of more than 1152 bins, or
+ * too few of them), events that are swept tile by tile one of 1024. */
 hough_status hough_launch_shape(const hough_ctx *ctx, int32_t *tile_rows, int32_t *wg_threads,
                                 int32_t *lds_bytes);
 

@@ -91,7 +91,9 @@ constexpr int kSmallCall = 8;
 // kDenseRho more bins reach T than its hot set holds, and calls of few workgroups
 // lose, from the fewest events on that any rows do; on 180 rows none does yet. Past
 // kDenseRows the row's sweep outweighs what overlaps with it, somewhere between
-// 2048 and 4096 rows. Both lines lie on the safe side of what was measured:
+// 2048 and 4096 rows (and lists are outgrown sooner: the largest bin, 1100 events of 65
+// hits on 1500 rows, T = 8: 437 / 763). Both lines lie on the safe side of what was
+// measured:
 //   27 hits, 110, 275        1024 events                              4096 events
 //   180 rows, 600 bins       96 / 62     144 / 92     258 / 184       318 / 174   482 / 271   922 / 610
 //   180 rows, 900 bins       92 / 59     135 / 86     214 / 146       303 / 165   465 / 259   759 / 453
@@ -106,6 +108,11 @@ constexpr int kSmallCall = 8;
 // (1024 events of 275 hits on 180 rows 237 / 146, on 1024 rows 450 / 2401). The same
 // line holds for local maxima below kDenseAny events; it leaves out 275 hits at 768
 // events on 1024 rows, which gain (above), and keeps 512 events, which lose, away.
+// At a low T the lists are outgrown by few hits: the largest bin takes the shape from
+// T = 4 on (1024 events of 27 hits on 1024 rows: T = 3 293 / 690, 4 242 / 86, 12 108 / 63),
+// windows wider than 3 x 3, whose events are then swept tile by tile, from T = 6 on
+// (7 x 7, 27 hits: T = 3 321 / 1887, 4 230 / 140; 132 hits: 4 1688 / 3645, 6 314 / 203).
+// 3 x 3 gains at every T measured (2 to 40: 1.2 to 5 times).
 // The host knows the events' number and mean size, not the largest, and a few
 // events that dwarf the rest end their call later in it (1 % of 200 tracks among 768
 // of 10 on 180 rows 486 / 613), or outgrow its shorter lists and are swept tile by
@@ -350,33 +357,6 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     const int row_bytes = 4 * c.pitch;
     hough_status st = make_shape(c, g.wg_threads > 0 ? g.wg_threads : 1024, g.tile_rows, lds_max, n_cu, c, why);
     if (st) return st;
-    // rows too long for sixteen waves' buffers and a hot set, or too few of them
-    // for a tile that holds those: as many waves as have room for both, or every
-    // event would take the tiled path (768 events of 272 hits on 2048 x 2048 bins:
-    // 2328 -> 425 us)
-    const bool long_rows = !c.stream_ok;
-    for (int t = 512; t >= 256 && g.wg_threads == 0 && g.tile_rows == 0 && g.peak_mode != 2 && !c.stream_ok; t /= 2) {
-        std::string none;
-        Shape f;
-        if (make_shape(c, t, 0, lds_max, n_cu, f, none) == HOUGH_OK && f.stream_ok) {
-            // (an event that outgrows the hot set's list is swept tile by tile here
-            // too, and slower by fewer waves: such calls keep the sixteen)
-            c.wide = c;
-            static_cast<Shape &>(c) = f;
-        }
-    }
-    // (beside sixteen waves: they are what its calls fall back to)
-    if (g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2 && c.wide.max_resident == 0) {
-        std::string none;
-        Shape f;
-        if (make_shape(c, kDenseThreads, 0, lds_max / 2, n_cu, f, none) == HOUGH_OK && f.stream_ok && f.big_ok &&
-            f.max_resident >= 2 * n_cu && raise_find_limit(c, f) == hipSuccess)
-            c.dense = f;
-    }
-    if (raise_find_limit(c, c) != hipSuccess || (c.wide.max_resident > 0 && raise_find_limit(c, c.wide) != hipSuccess)) {
-        why = "hipFuncSetAttribute failed for the finder kernel";
-        return HOUGH_ERR_DEVICE;
-    }
     // |rho| <= r (1 + 2^-24)^3 for r = sqrt(phi^2 + z^2); a rho at least
     // delta inside [rho_min, rho_max] gives a bin in [0, n_rho) after the
     // rounded subtraction and multiplication by inv_w (relative error
@@ -387,16 +367,47 @@ hough_status choose_shape(Ctx &c, std::string &why) {
         const double rmax = std::min(-(double)g.rho_min, (double)g.rho_max) - delta;
         c.safe_r2 = rmax > 0.0 ? (rmax / (1.0 + 1e-6)) * (rmax / (1.0 + 1e-6)) : -1.0;
     }
+    // a rho range that the vanes' azimuths alone leave: nearly every event holds hits
+    // whose votes leave it, and such an event is swept tile by tile
+    const float phi_max = *std::max_element(c.phi_v.begin(), c.phi_v.end());
+    const bool streams = c.safe_r2 >= (double)phi_max * phi_max;
+    // rows too long for sixteen waves' buffers and a hot set, or too few of them
+    // for a tile that holds those: as many waves as have room for both, or every
+    // event would take the tiled path (768 events of 272 hits on 2048 x 2048 bins:
+    // 2328 -> 425 us). At T = 1 every voted bin is hot and nearly every event outgrows
+    // the lists (1100 events of 65 hits on 33 x 4096 bins 4.4 ms tiled, 9.8 after a
+    // try); a configured split sweep (one workgroup of 512 threads an event, T = 40,
+    // 64 events of 77 hits on 360 x 4096 bins) is slower than the tiles, 0.48 / 0.78 ms
+    const bool fewer = g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2 && streams && g.min_votes >= 2;
+    for (int t = 512; t >= 256 && fewer && !c.stream_ok; t /= 2) {
+        std::string none;
+        Shape f;
+        if (make_shape(c, t, 0, lds_max, n_cu, f, none) == HOUGH_OK && f.stream_ok) {
+            // (an event that is swept tile by tile for all that goes to the
+            // sixteen waves, which are faster at it)
+            c.wide = c;
+            static_cast<Shape &>(c) = f;
+        }
+    }
+    // (beside sixteen waves: they are what its calls fall back to)
+    if (g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2 && c.wide.max_resident == 0 &&
+        g.n_theta <= kDenseRows && streams && (g.peak_mode == 0 ? g.min_votes >= 4 : g.nms_radius <= 1 || g.min_votes >= 6)) {
+        std::string none;
+        Shape f;
+        if (make_shape(c, kDenseThreads, 0, lds_max / 2, n_cu, f, none) == HOUGH_OK && f.stream_ok && f.big_ok &&
+            f.max_resident >= 2 * n_cu && raise_find_limit(c, f) == hipSuccess)
+            c.dense = f;
+    }
+    if (raise_find_limit(c, c) != hipSuccess || (c.wide.max_resident > 0 && raise_find_limit(c, c.wide) != hipSuccess)) {
+        why = "hipFuncSetAttribute failed for the finder kernel";
+        return HOUGH_ERR_DEVICE;
+    }
     c.sweep_groups = c.stream_ok ? g.sweep_groups : 0;
     c.sweep_threads = g.sweep_threads > 0 ? g.sweep_threads : 256;
     if (c.sweep_groups > 0) {
         const int sl = hough::sweep_lds_bytes(c.sweep_threads, c.pitch);
-        if (sl + kStaticLds > lds_max && long_rows) {
-            c.sweep_groups = 0;   // as on the tiled path, which such rows would take with sixteen waves
-        } else if (sl + kStaticLds > lds_max) {
-            why = "sweep row buffers do not fit in LDS";
-            return HOUGH_ERR_INVALID_ARG;
-        } else if (raise_sweep_limit(c, c.sweep_threads, sl) != hipSuccess) {
+        if (sl + kStaticLds > lds_max) { why = "sweep row buffers do not fit in LDS"; return HOUGH_ERR_INVALID_ARG; }
+        if (raise_sweep_limit(c, c.sweep_threads, sl) != hipSuccess) {
             why = "hipFuncSetAttribute failed for the sweep kernel";
             return HOUGH_ERR_DEVICE;
         }
@@ -504,7 +515,7 @@ bool takes_dense(const Ctx &c, int64_t n_events, int64_t n_hits) {
     if (c.dense.max_resident == 0 || n_events < kDenseEvents) return false;
     if (n_hits > n_events * dense_hits(c, n_hits)) return false;   // some event has more than it may
     const bool wide = c.cfg.n_rho >= kDenseRho;
-    if (c.cfg.peak_mode == 1 && c.cfg.n_theta <= kDenseRows && n_events >= (wide ? kDenseAny : kDenseAnyNarrow)) return true;
+    if (c.cfg.peak_mode == 1 && n_events >= (wide ? kDenseAny : kDenseAnyNarrow)) return true;
     return wide && n_hits <= kDenseHits * n_events && n_hits * c.cfg.n_theta <= kDenseVotes * n_events;
 }
 
@@ -529,8 +540,8 @@ size_t layout_workspace(const Ctx &c, int64_t nh, int64_t ne, int32_t big_pk, ch
     const size_t o_pflags = take(4 * ((size_t)slots + 2 * kBandCall));
     const size_t o_bcnt = take(4 * (size_t)kBandCall * 16);
     const size_t o_pool = take((size_t)slots * (size_t)slot_bytes);
-    const bool pick = dense || (c.wide.max_resident > 0 && ne > 1 && !bare);
-    const size_t o_pick = pick ? take(sizeof(hough::Pick)) : 0;
+    const bool pick = dense || (c.wide.max_resident > 0 && !bare);
+    const size_t o_pick = pick ? take(sizeof(hough::Pick) + 4 * (size_t)ne) : 0;
     if (base != nullptr) {
         w->base = base;
         w->bytes = off;
@@ -676,10 +687,13 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     // (the served form's launches overlap on the device and keep the default
     // shape; so does a workspace without a slot for each dense workgroup)
     const bool dense = longest_first && w.dense && takes_dense(c, n_events, n_total);
-    // long rows: events that outgrow the shape's list, if there are any. Alone, the
-    // host knows; among others the device does (or the tiled shape takes all)
-    const bool wide = c.wide.max_resident > 0 && n_total > list_hits(c);
-    const bool pick = dense || (wide && n_events > 1 && w.pick != nullptr);
+    // long rows: an event that the shape's list does not hold, or that it would sweep
+    // tile by tile for another reason, goes to the tiled shape of sixteen waves (a lone one
+    // of too many hits by itself, and every one where the workspace has no second list).
+    // A dense call's few tiled events stay: in the second launch they would come after
+    // the others (776 events of 360 x 1000 bins, 3 % with a hit off the grid: 75 / 113)
+    const bool wide = c.wide.max_resident > 0;
+    const bool pick = dense || (wide && w.pick != nullptr && !(n_events == 1 && n_total > list_hits(c)));
     const Shape &f = dense ? c.dense : (wide && !pick ? c.wide : c);
     const Shape &other = dense ? c : c.wide;
     hough::FindArgs a = find_args(c, f, w);
@@ -727,7 +741,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     }
     hough::FindArgs list{};
     const bool ordered = longest_first && (dense || n_events > std::max(f.max_resident, kOrderMin));
-    if (ordered || pick) {
+    if (ordered || (pick && n_events > 0)) {
         // the longest events start first and the short ones fill the CUs at
         // the end of the launch (with no more events than resident
         // workgroups every event starts at once and the order is moot)
@@ -737,7 +751,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
             list = a;
             list.g_hs = nullptr;
             set_shape(list, other);
-            so = hough::launch_order_pick(list, w.order, w.pick, dense ? dense_hits(c, n_total) : list_hits(c), s);
+            so = hough::launch_order_pick(list, w.order, w.pick, dense ? dense_hits(c, n_total) : INT64_MAX, !dense, s);
             a.pick = w.pick;
         } else {
             so = hough::launch_order(offsets, n_events, w.order, s);
@@ -753,7 +767,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     hipError_t st;
     if (c.cfg.peak_mode == 2) {
         st = hough::launch_find_cf(a, c.wg_threads, c.lds_bytes, s);
-    } else if (pick) {
+    } else if (pick && n_events > 0) {
         st = hough::launch_picked(a, f.wg_threads, f.lds_bytes, s);
         if (st == hipSuccess)
             st = hough::launch_list(list, w.pick, other.max_resident, other.wg_threads, other.lds_bytes, s);

@@ -112,7 +112,7 @@ struct FindArgs {
     // kernel's); at least 512 (the register batch) when k_band does not run
     int32_t band_min;
     // calls that enqueue two shapes: the choice that k_order_pick made, or NULL
-    const struct Pick *pick;
+    struct Pick *pick;
 };
 
 // Records the event's start and retire clock stamps when the call asked for
@@ -125,11 +125,15 @@ __device__ inline void stamp_event(const FindArgs &A, int e, unsigned long long 
 }
 
 // The choice between a call's two shapes, made on the device: the first unless an
-// event has too many hits for it.
+// event has too many hits for it. With defer, an event that the first would sweep
+// tile by tile goes to the second as well; the list of those, n_events ints, follows.
 struct Pick {
-    int32_t first;   // 1: k_picked runs, 0: k_list
-    int32_t next;    // k_list: the next event's place in order[]
-    FindArgs list;   // its arguments
+    int32_t first;      // 1: k_picked runs, then k_list on what it left; 0: k_list on all
+    int32_t next;       // k_list: the next event's place in order[] or again[]
+    int32_t defer;
+    int32_t deferred;   // events in again[]
+    int32_t *again;
+    FindArgs list;      // k_list's arguments
 };
 
 struct DumpArgs {
@@ -183,13 +187,14 @@ hipError_t launch_clear_workspace(long long *err, int32_t *g_cnt, int32_t *g_fla
                                   int32_t *pool_flags, int32_t slots, hipStream_t s);
 // order[0, n_events): the events by descending hit count (device offsets). With
 // pick, also the choice of a call's shape: the first if no event has more than
-// pick_hits hits; list are k_list's arguments.
+// pick_hits hits; list are k_list's arguments (see Pick).
 hipError_t launch_order(const int64_t *offsets, int32_t n_events, int32_t *order, hipStream_t s);
-hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, hipStream_t s);
+hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, bool defer,
+                             hipStream_t s);
 // The finder on a's events, in a.order, if the first shape was picked (256 or 512 threads).
 hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, hipStream_t s);
-// The finder on list's events, in list.order, if it was not: `groups` workgroups
-// of 1024 threads that take one event after the other.
+// The finder on list's events, in list.order, if it was not, else on those that it
+// left: `groups` workgroups of 1024 threads that take one event after the other.
 hipError_t launch_list(const FindArgs &list, Pick *pick, int groups, int wg_threads, int lds_bytes, hipStream_t s);
 hipError_t launch_compact(const CompactArgs &a, hipStream_t s);
 hipError_t launch_dump(const DumpArgs &a, int lds_bytes, hipStream_t s);

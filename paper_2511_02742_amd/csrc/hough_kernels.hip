@@ -2765,7 +2765,9 @@ __device__ __forceinline__ Lds find_lds(const FindArgs &A) {
 // searches the largest bin (peak_mode 0), else every local maximum (1); one
 // kernel for both held registers of the one in the loops of the other (Poisson(20)
 // batch 699 -> 723 us with argmax_loop beside the window test).
-template <int NT, bool MAX>
+// DEFER: an event that would be swept tile by tile is left for the call's second
+// shape if the call asks for that (k_list finds it in A.pick and starts it over).
+template <int NT, bool MAX, bool DEFER = false>
 __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__restrict__ cs, const Lds &L, Shared &sh,
                                            int e, int64_t b, int64_t n64) {
     constexpr int NW = NT / kWave;
@@ -3125,6 +3127,17 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                 continue;
             }
         }
+        if (DEFER && !done && A.pick->defer != 0) {
+            release_slot(A, slot >= 0 ? slot : sh.rslot);
+            if (tid_x() == 0) {
+                if (A.g_cnt != nullptr) {
+                    A.g_cnt[e] = 0;
+                    A.g_flag[e] = 0;
+                }
+                A.pick->again[atomicAdd(&A.pick->deferred, 1)] = e;
+            }
+            return;
+        }
         if (!done) {
             hs_valid = false;
             evals += (unsigned long long)n_alive * (unsigned long long)A.n_theta;
@@ -3255,26 +3268,28 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     if (A.pick->first == 0) return;
     const int e = __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]);
     const int64_t b = uniform64(A.offsets[e]);
-    find_event<NT, MAX>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
+    find_event<NT, MAX, true>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
 }
 
 // The events of a call that k_order_pick sent past the first shape, the longest
-// first, by as many workgroups as are resident at once (k_find with a workgroup per
+// first, or those that k_picked left, by as many workgroups as are resident at once (k_find with a workgroup per
 // event in its place cost a call that takes the dense shape 10 us at 4096 events,
 // this 3; where it runs, its event function being a call, it takes 1 to 4 % longer).
 constexpr int kListThreads = 1024;
 template <bool MAX>
 __global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_list(Pick *P) {
-    if (P->first != 0) return;
     __shared__ int at;
     const FindArgs &A = tw::const_args(&P->list);
+    const bool all = __builtin_amdgcn_readfirstlane(P->first) == 0;
+    const int n = all ? A.n_events : __builtin_amdgcn_readfirstlane(P->deferred);
+    if ((int)blockIdx.x >= n) return;
     for (;;) {
         if (tid_x() == 0) at = atomicAdd(&P->next, 1);
         __syncthreads();
         const int i = __builtin_amdgcn_readfirstlane(at);
         __syncthreads();
-        if (i >= A.n_events) return;
-        const int e = __builtin_amdgcn_readfirstlane(A.order[i]);
+        if (i >= n) return;
+        const int e = __builtin_amdgcn_readfirstlane(all ? A.order[i] : P->again[i]);
         const int64_t b = uniform64(A.offsets[e]);
         find_event_call<kListThreads, MAX, 1>(&P->list, e, b, uniform64(A.offsets[e + 1]) - b);
         __syncthreads();
@@ -3745,6 +3760,7 @@ __device__ __forceinline__ void order_events(const int64_t *offsets, int32_t n_e
         if (t == 0) {
             pick->first = over ? 0 : 1;
             pick->next = 0;
+            pick->deferred = 0;
         }
     } else {
         __syncthreads();
@@ -3770,8 +3786,13 @@ __global__ __launch_bounds__(kOrderBins) void k_order(const int64_t *offsets, in
 }
 
 // The same, and which of the call's two shapes runs.
-__global__ __launch_bounds__(kOrderBins) void k_order_pick(FindArgs list, int32_t *order, Pick *pick, int64_t pick_hits) {
-    if (tid_x() == 0) pick->list = list;
+__global__ __launch_bounds__(kOrderBins) void k_order_pick(FindArgs list, int32_t *order, Pick *pick, int64_t pick_hits,
+                                                           int32_t defer) {
+    if (tid_x() == 0) {
+        pick->list = list;
+        pick->again = reinterpret_cast<int32_t *>(pick + 1);
+        pick->defer = defer;
+    }
     order_events<true>(list.offsets, list.n_events, order, pick, pick_hits);
 }
 
@@ -3798,8 +3819,9 @@ hipError_t launch_order(const int64_t *offsets, int32_t n_events, int32_t *order
     return hipGetLastError();
 }
 
-hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, hipStream_t s) {
-    hipLaunchKernelGGL(k_order_pick, dim3(1), dim3(kOrderBins), 0, s, list, order, pick, pick_hits);
+hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, bool defer,
+                             hipStream_t s) {
+    hipLaunchKernelGGL(k_order_pick, dim3(1), dim3(kOrderBins), 0, s, list, order, pick, pick_hits, defer ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -101,8 +101,9 @@ hipError_t launch_order(const int64_t *, int32_t n, int32_t *, hipStream_t) {
     note("{\"launch\": \"order\", \"events\": %d}", n);
     return hipSuccess;
 }
-hipError_t launch_order_pick(const FindArgs &a, int32_t *, Pick *, int64_t hits, hipStream_t) {
-    note("{\"launch\": \"order_pick\", \"events\": %d, \"hits\": %lld}", a.n_events, (long long)hits);
+hipError_t launch_order_pick(const FindArgs &a, int32_t *, Pick *, int64_t hits, bool defer, hipStream_t) {
+    note("{\"launch\": \"order_pick\", \"events\": %d, \"hits\": %lld, \"defer\": %d}", a.n_events, (long long)hits,
+         defer);
     return hipSuccess;
 }
 hipError_t launch_picked(const FindArgs &a, int threads, int lds, hipStream_t) {

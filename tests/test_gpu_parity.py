@@ -870,7 +870,7 @@ def test_a_large_event_among_many_small_ones(gpu_available, kw, n_events, sizes)
 @pytest.mark.parametrize("n_events", [2, 9, 70, 300])
 def test_large_events_among_others_on_long_rows(gpu_available, kw, list_hits, n_events):
     # a call on rows too long for sixteen waves that holds an event at the size
-    # its shape's list holds, and one more hit (the device then picks the tiled
+    # its shape's list holds, and one more hit (it is then left to the tiled
     # shape): the bytes of the one-shape call, also without allocation
     import torch
     small = [eventgen.pileup_event(64_000 + i, n_tracks=n) for i, n in enumerate((3, 12, 30, 60, 90))]
@@ -888,8 +888,8 @@ def test_large_events_among_others_on_long_rows(gpu_available, kw, list_hits, n_
         for got in (own.find(*t).to_host(), own.find(*t, noalloc=True).to_host()):
             assert got[2]["status"] == 0 and got[0].tobytes() == want[0].tobytes() and np.array_equal(got[1], want[1]), n
             assert got[2]["iters"] == want[2]["iters"]
-        if n_events >= 70:   # every event by the tiled sweep where the large one outgrows the list, else none of the small
-            assert (own.find(*t).to_host()[2]["tiled"] >= n_events) == (n > list_hits)
+        if n > list_hits:   # the large event alone is swept tile by tile
+            assert 0 < own.find(*t).to_host()[2]["tiled"] < want[2]["tiled"]
 
 
 @pytest.mark.parametrize("kw", [{}, {"n_theta": 180, "n_rho": 1000}, {"n_theta": 600, "n_rho": 700}, {"n_rho": 1500}])
@@ -934,3 +934,36 @@ def test_many_events_on_few_rows(gpu_available, n_theta, n_rho, peak_mode):
         got, want = own.find(*t).to_host(), one.find(*t).to_host()
         assert got[2]["status"] == want[2]["status"] == 0 and got[2]["candidates"] == want[2]["candidates"]
         assert got[0].tobytes() == want[0].tobytes() and np.array_equal(got[1], want[1]) and got[2]["iters"] == want[2]["iters"]
+
+
+@pytest.mark.parametrize("kw", [dict(n_theta=200, n_rho=1500, min_votes=2), dict(n_theta=200, n_rho=3000, min_votes=1),
+                                dict(n_theta=200, n_rho=1300, rho_min=-250.0, rho_max=260.0), dict(n_theta=9, n_rho=1024),
+                                dict(n_theta=200, n_rho=1500, peak_mode=0, min_votes=2, rho_min=-250.0, rho_max=260.0),
+                                dict(n_theta=900, n_rho=1000, nms_radius=3, min_votes=4), dict(n_theta=180, n_rho=1000, min_votes=2),
+                                dict(n_theta=180, n_rho=1000, rho_min=-250.0, rho_max=260.0)])
+@pytest.mark.parametrize("n_events", [1, 5, 70, 800])
+def test_events_left_to_the_second_shape(gpu_available, kw, n_events):
+    # calls of two shapes whose first would sweep some or all events tile by tile: hits
+    # that leave the grid, more bins at T than its hot set holds, wide windows. They
+    # start over in the second: the bytes of the one-shape call, twice, and captured
+    import torch
+    from paper_2511_02742_amd.hough import HoughFinder
+    pool = [eventgen.pileup_event(67_000 + i, n_tracks=n) for i, n in enumerate((2, 7, 15, 1, 25, 40))]
+    own, one = finder(**kw), finder(wg_threads=1024, **kw)
+    dev = torch.device("cuda", 0)
+    b = eventgen.make_batch([pool[(i * 5 + n_events) % 6] for i in range(n_events)])
+    t = [torch.from_numpy(x).to(dev) for x in (b.z, b.vane, b.offsets)]
+    want = one.find(*t).to_host()
+    assert want[2]["status"] == 0 and (n_events == 1 or want[2]["candidates"] > 0)
+    for got in (own.find(*t).to_host(), own.find(*t, noalloc=True).to_host(), own.find(*t).to_host()):
+        assert got[2]["status"] == 0 and got[0].tobytes() == want[0].tobytes() and np.array_equal(got[1], want[1])
+        assert got[2]["iters"] == want[2]["iters"]
+    graph = HoughFinder(0, **kw).capture(*t)
+    for _ in range(3):
+        graph.out.cand.zero_()
+        own.find(*t)
+        r = graph.launch()
+        torch.cuda.synchronize()
+        r = r.to_host()
+        assert r[0].tobytes() == want[0].tobytes() and np.array_equal(r[1], want[1])
+    graph.close()

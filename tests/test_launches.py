@@ -90,7 +90,10 @@ DENSE = [
     ({}, 1024, 1024 * 2560 + 1, None),                # some event has more
     ({}, 1023, 1023 * 137, None),
     ({"n_theta": 1025}, 1024, 1024 * 137, None),
-    ({"n_theta": 1025}, 1024, 1024 * 100, 380),
+    ({"n_theta": 1025}, 1024, 1024 * 100, None),
+    ({"rho_min": -300.0, "rho_max": 300.0}, 1024, 1024 * 137, None),   # azimuths to 351 degrees leave the grid
+    ({"rho_min": -360.0, "rho_max": 360.0}, 1024, 1024 * 137, 520),
+    ({"rho_min": -300.0, "rho_max": 300.0, "phi_unit": 1}, 1024, 1024 * 137, 520),
     ({"n_rho": 999}, 3071, 3071 * 27, None),
     ({"n_rho": 999}, 3072, 3072 * 27, 352),
     ({"n_rho": 1000, "n_theta": 180}, 768, 768 * 320, 912),
@@ -105,6 +108,10 @@ DENSE = [
     ({"tile_rows": 14}, 4096, 4096 * 110, None),
     ({"sweep_groups": 1}, 4096, 4096 * 110, None),
     ({"nms_radius": 3}, 4096, 4096 * 110, 1672),
+    ({"nms_radius": 3, "min_votes": 5}, 4096, 4096 * 110, None),       # wide windows from T = 6 on,
+    ({"nms_radius": 1, "min_votes": 2}, 4096, 4096 * 110, 1672),
+    ({"peak_mode": ARGMAX, "min_votes": 4}, 1024, 1024 * 110, 2560),   # the largest bin from T = 4
+    ({"peak_mode": ARGMAX, "min_votes": 3}, 1024, 1024 * 110, None),
     ({"n_rho": 1000, "n_theta": 180, "peak_mode": 2}, 4096, 4096 * 110, None),
 ]
 
@@ -120,7 +127,7 @@ def test_dense_shape(host, cfg, events, hits, most):
         return
     assert kinds == ["order_pick", "picked", "list", "compact"]
     order, dense, rest, compact = got
-    assert order["hits"] == most and order["events"] == dense["events"] == events
+    assert order["hits"] == most and order["defer"] == 0 and order["events"] == dense["events"] == events
     assert compact["ordered"] == 1
     # two workgroups per CU, a slot for each; the other shape is the context's own
     assert dense["threads"] == 512 and dense["lds"] <= (160 << 10) // 2 - 2048 and rest["threads"] == 1024 and rest["groups"] == 256
@@ -148,6 +155,15 @@ def test_dense_shape_needs_its_workspace(host):
     host.lib.hough_destroy(h)
 
 
+@pytest.mark.parametrize("cfg,threads", [({}, 512), ({"min_votes": 2}, 512), ({"min_votes": 1}, 1024), ({"sweep_groups": 2}, 1024),
+                                         ({"rho_min": -350.0, "rho_max": 350.0}, 1024), ({"rho_min": -360.0, "rho_max": 360.0}, 512)])
+def test_long_rows_that_would_be_tiled_anyway(host, cfg, threads):
+    """Where nearly every event would outgrow the lists or leaves the grid, long
+    rows keep sixteen waves, as with a configured split sweep."""
+    got = [x for x in host.calls(64, 9000, n_rho=2048, **cfg) if x["launch"] in ("find", "picked")]
+    assert [x["threads"] for x in got] == [threads]
+
+
 # Long rows: (rho bins, threads of the shape that streams them, hits its list holds)
 LONG = [(1160, 512, 2560), (2048, 512, 4096), (2304, 512, 4096), (2400, 256, 2560), (4096, 256, 4096)]
 
@@ -155,24 +171,23 @@ LONG = [(1160, 512, 2560), (2048, 512, 4096), (2304, 512, 4096), (2400, 256, 256
 @pytest.mark.parametrize("n_rho,threads,most", LONG)
 @pytest.mark.parametrize("mode", [NMS, ARGMAX])
 def test_large_events_on_long_rows(host, n_rho, threads, most, mode):
-    """An event that outgrows the list of the shape for long rows is swept tile
-    by tile in either shape, and faster by sixteen waves: alone the host sends it there,
-    a call that may hold one enqueues both shapes."""
+    """An event that the shape for long rows would sweep tile by tile (it outgrows
+    its list, say) is faster swept so by sixteen waves: alone the host sends it there, a
+    call enqueues both shapes, and the first leaves such events to the second."""
     def of(events, hits, **kw):
         return [x for x in host.calls(events, hits, n_rho=n_rho, peak_mode=mode, **kw) if x["launch"] not in ("sweep", "band")]
-    # alone, up to the list's size and past it
-    assert [x["threads"] for x in of(1, most)] == [threads]
-    assert [(x["threads"], x["stream_ok"]) for x in of(1, most + 1)] == [(1024, 0)]
-    # a few that cannot hold one, and some that may
-    assert [x["launch"] for x in of(4, most)] == ["find", "compact"]
-    for n in (2, 64, 65, 300):
-        got = of(n, most + 1)
-        assert [x["launch"] for x in got] == ["order_pick", "picked", "list", "compact"]
-        assert got[0]["hits"] == most and got[1]["threads"] == threads and got[1]["hs_cap"] // 64 * 64 >= most - 512
-        assert got[2]["threads"] == 1024 and got[2]["stream_ok"] == 0 and got[2]["split"] == 0
-        assert got[3]["ordered"] == (1 if n > 256 else 0)
-    # where the choice does not fit the fixed scratch, the tiled shape takes the call
-    assert [x["launch"] for x in of(64, most + 1, noalloc=True)] == ["order_pick", "picked", "list", "compact"]
+    # alone past the list's size: the host knows
+    assert [(x["launch"], x["threads"], x["stream_ok"]) for x in of(1, most + 1)] == [("find", 1024, 0)]
+    for n, hits in ((1, most), (2, 300), (4, most + 1), (64, 9000), (300, 90000)):
+        for noalloc in (False, True):
+            got = of(n, hits, noalloc=noalloc)
+            assert [x["launch"] for x in got] == ["order_pick", "picked", "list"] + (["compact"] if n > 1 else [])
+            assert got[0]["hits"] == 2**63 - 1 and got[0]["defer"] == 1 and got[1]["threads"] == threads
+            assert got[1]["hs_cap"] // 64 * 64 >= most - 512
+            assert got[2]["threads"] == 1024 and got[2]["stream_ok"] == 0 and got[2]["split"] == 0
+            assert n == 1 or got[3]["ordered"] == (1 if n > 256 else 0)
+    # where the second list does not fit the fixed scratch, the tiled shape takes the call
+    assert [(x["launch"], x.get("threads")) for x in of(64, 1 << 20, noalloc=True)][-2] in (("list", 1024), ("find", 1024))
     # configured shapes are what they were
     assert [x["threads"] for x in of(1, most + 1, wg_threads=256) + of(2, most + 1, wg_threads=512)[:1]] == [256, 512]
 
