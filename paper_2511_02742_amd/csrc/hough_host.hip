@@ -751,7 +751,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
             list = a;
             list.g_hs = nullptr;
             set_shape(list, other);
-            so = hough::launch_order_pick(list, w.order, w.pick, dense ? dense_hits(c, n_total) : INT64_MAX, !dense, s);
+            so = hough::launch_order_pick(list, w.order, w.pick, dense ? dense_hits(c, n_total) : INT64_MAX, s);
             a.pick = w.pick;
         } else {
             so = hough::launch_order(offsets, n_events, w.order, s);
@@ -768,7 +768,7 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     if (c.cfg.peak_mode == 2) {
         st = hough::launch_find_cf(a, c.wg_threads, c.lds_bytes, s);
     } else if (pick && n_events > 0) {
-        st = hough::launch_picked(a, f.wg_threads, f.lds_bytes, s);
+        st = hough::launch_picked(a, f.wg_threads, f.lds_bytes, !dense, s);
         if (st == hipSuccess)
             st = hough::launch_list(list, w.pick, other.max_resident, other.wg_threads, other.lds_bytes, s);
     } else {

@@ -125,12 +125,11 @@ __device__ inline void stamp_event(const FindArgs &A, int e, unsigned long long 
 }
 
 // The choice between a call's two shapes, made on the device: the first unless an
-// event has too many hits for it. With defer, an event that the first would sweep
+// event has too many hits for it. On long rows an event that the first would sweep
 // tile by tile goes to the second as well; the list of those, n_events ints, follows.
 struct Pick {
     int32_t first;      // 1: k_picked runs, then k_list on what it left; 0: k_list on all
     int32_t next;       // k_list: the next event's place in order[] or again[]
-    int32_t defer;
     int32_t deferred;   // events in again[]
     int32_t *again;
     FindArgs list;      // k_list's arguments
@@ -189,10 +188,10 @@ hipError_t launch_clear_workspace(long long *err, int32_t *g_cnt, int32_t *g_fla
 // pick, also the choice of a call's shape: the first if no event has more than
 // pick_hits hits; list are k_list's arguments (see Pick).
 hipError_t launch_order(const int64_t *offsets, int32_t n_events, int32_t *order, hipStream_t s);
-hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, bool defer,
-                             hipStream_t s);
-// The finder on a's events, in a.order, if the first shape was picked (256 or 512 threads).
-hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, hipStream_t s);
+hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, hipStream_t s);
+// The finder on a's events, in a.order, if the first shape was picked (512 threads,
+// or with defer, see Pick, also 256).
+hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, bool defer, hipStream_t s);
 // The finder on list's events, in list.order, if it was not, else on those that it
 // left: `groups` workgroups of 1024 threads that take one event after the other.
 hipError_t launch_list(const FindArgs &list, Pick *pick, int groups, int wg_threads, int lds_bytes, hipStream_t s);

@@ -35,6 +35,7 @@
 #include "hough_wave.h"
 
 #include <algorithm>
+#include <initializer_list>
 #include <type_traits>
 
 namespace hough {
@@ -2766,7 +2767,7 @@ __device__ __forceinline__ Lds find_lds(const FindArgs &A) {
 // kernel for both held registers of the one in the loops of the other (Poisson(20)
 // batch 699 -> 723 us with argmax_loop beside the window test).
 // DEFER: an event that would be swept tile by tile is left for the call's second
-// shape if the call asks for that (k_list finds it in A.pick and starts it over).
+// shape (k_list finds it in A.pick and starts it over).
 template <int NT, bool MAX, bool DEFER = false>
 __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__restrict__ cs, const Lds &L, Shared &sh,
                                            int e, int64_t b, int64_t n64) {
@@ -3127,7 +3128,7 @@ __device__ __forceinline__ void find_event(const FindArgs &A, const float2 *__re
                 continue;
             }
         }
-        if (DEFER && !done && A.pick->defer != 0) {
+        if (DEFER && !done) {
             release_slot(A, slot >= 0 ? slot : sh.rslot);
             if (tid_x() == 0) {
                 if (A.g_cnt != nullptr) {
@@ -3261,14 +3262,14 @@ __device__ __noinline__ void find_event_call(const FindArgs *A, int e, int64_t b
 // The first of the two shapes of a call that enqueues both: k_order_pick's choice
 // decides. (In k_find the test cost calls of one shape 1 %: the compiler held other
 // values.)
-template <int NT, bool MAX>
+template <int NT, bool MAX, bool DEFER>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_picked(FindArgs A,
                                                                                      const float2 *__restrict__ cs) {
     __shared__ Shared sh;
     if (A.pick->first == 0) return;
     const int e = __builtin_amdgcn_readfirstlane(A.order[blockIdx.x]);
     const int64_t b = uniform64(A.offsets[e]);
-    find_event<NT, MAX, true>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
+    find_event<NT, MAX, DEFER>(A, cs, find_lds(A), sh, e, b, uniform64(A.offsets[e + 1]) - b);
 }
 
 // The events of a call that k_order_pick sent past the first shape, the longest
@@ -3786,12 +3787,10 @@ __global__ __launch_bounds__(kOrderBins) void k_order(const int64_t *offsets, in
 }
 
 // The same, and which of the call's two shapes runs.
-__global__ __launch_bounds__(kOrderBins) void k_order_pick(FindArgs list, int32_t *order, Pick *pick, int64_t pick_hits,
-                                                           int32_t defer) {
+__global__ __launch_bounds__(kOrderBins) void k_order_pick(FindArgs list, int32_t *order, Pick *pick, int64_t pick_hits) {
     if (tid_x() == 0) {
         pick->list = list;
         pick->again = reinterpret_cast<int32_t *>(pick + 1);
-        pick->defer = defer;
     }
     order_events<true>(list.offsets, list.n_events, order, pick, pick_hits);
 }
@@ -3819,9 +3818,8 @@ hipError_t launch_order(const int64_t *offsets, int32_t n_events, int32_t *order
     return hipGetLastError();
 }
 
-hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, bool defer,
-                             hipStream_t s) {
-    hipLaunchKernelGGL(k_order_pick, dim3(1), dim3(kOrderBins), 0, s, list, order, pick, pick_hits, defer ? 1 : 0);
+hipError_t launch_order_pick(const FindArgs &list, int32_t *order, Pick *pick, int64_t pick_hits, hipStream_t s) {
+    hipLaunchKernelGGL(k_order_pick, dim3(1), dim3(kOrderBins), 0, s, list, order, pick, pick_hits);
     return hipGetLastError();
 }
 
@@ -3871,7 +3869,8 @@ hipError_t find_blocks_per_cu(int wg_threads, bool argmax, int lds_bytes, int *b
             if (e == hipSuccess) e = query(kernel, &n);
             *most = std::max(*most, n);
         };
-        if constexpr (nt() < 1024) argmax ? more(k_picked<nt(), true>) : more(k_picked<nt(), false>);
+        if constexpr (nt() < 1024) argmax ? more(k_picked<nt(), true, true>) : more(k_picked<nt(), false, true>);
+        if constexpr (nt() == 512) argmax ? more(k_picked<nt(), true, false>) : more(k_picked<nt(), false, false>);
         if constexpr (nt() == kListThreads) argmax ? more(k_list<true>) : more(k_list<false>);
         argmax ? more(k_tw_run<nt(), true>) : more(k_tw_run<nt(), false>);
         return e;
@@ -3880,19 +3879,25 @@ hipError_t find_blocks_per_cu(int wg_threads, bool argmax, int lds_bytes, int *b
 
 hipError_t set_find_lds_limit(int wg_threads, int lds_bytes) {
     return with_threads(wg_threads, [&](auto nt) {
+        auto raise = [&](std::initializer_list<const void *> kernels) {
+            hipError_t e = hipSuccess;
+            for (const void *f : kernels)
+                if (e == hipSuccess) e = lds_limit(f, lds_bytes);
+            return e;
+        };
+        hipError_t e = raise({reinterpret_cast<const void *>(k_find<nt()>), reinterpret_cast<const void *>(k_argmax<nt()>)});
         if constexpr (nt() < 1024)
-            for (const void *f : {reinterpret_cast<const void *>(k_picked<nt(), false>),
-                                  reinterpret_cast<const void *>(k_picked<nt(), true>)}) {
-                const hipError_t e = lds_limit(f, lds_bytes);
-                if (e != hipSuccess) return e;
-            }
+            if (e == hipSuccess)
+                e = raise({reinterpret_cast<const void *>(k_picked<nt(), false, true>),
+                           reinterpret_cast<const void *>(k_picked<nt(), true, true>)});
+        if constexpr (nt() == 512)
+            if (e == hipSuccess)
+                e = raise({reinterpret_cast<const void *>(k_picked<nt(), false, false>),
+                           reinterpret_cast<const void *>(k_picked<nt(), true, false>)});
         if constexpr (nt() == kListThreads)
-            for (const void *f : {reinterpret_cast<const void *>(k_list<false>), reinterpret_cast<const void *>(k_list<true>)}) {
-                const hipError_t e = lds_limit(f, lds_bytes);
-                if (e != hipSuccess) return e;
-            }
-        const hipError_t e = lds_limit(reinterpret_cast<const void *>(k_find<nt()>), lds_bytes);
-        return e != hipSuccess ? e : lds_limit(reinterpret_cast<const void *>(k_argmax<nt()>), lds_bytes);
+            if (e == hipSuccess)
+                e = raise({reinterpret_cast<const void *>(k_list<false>), reinterpret_cast<const void *>(k_list<true>)});
+        return e;
     });
 }
 
@@ -3929,16 +3934,17 @@ hipError_t launch_find(const FindArgs &a, int wg_threads, int lds_bytes, hipStre
     });
 }
 
-hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, hipStream_t s) {
-    auto launch = [&](auto nt) {
+hipError_t launch_picked(const FindArgs &a, int wg_threads, int lds_bytes, bool defer, hipStream_t s) {
+    auto launch = [&](auto nt, auto df) {
         if (a.peak_mode == 0)
-            hipLaunchKernelGGL((k_picked<nt(), true>), dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
+            hipLaunchKernelGGL((k_picked<nt(), true, df()>), dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
         else
-            hipLaunchKernelGGL((k_picked<nt(), false>), dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
+            hipLaunchKernelGGL((k_picked<nt(), false, df()>), dim3(a.n_events), dim3(nt()), lds_bytes, s, a, a.cs);
         return hipGetLastError();
     };
-    if (wg_threads == 512) return launch(std::integral_constant<int, 512>());
-    if (wg_threads == 256) return launch(std::integral_constant<int, 256>());
+    constexpr std::integral_constant<int, 512> k512;
+    if (wg_threads == 512) return defer ? launch(k512, std::true_type()) : launch(k512, std::false_type());
+    if (wg_threads == 256 && defer) return launch(std::integral_constant<int, 256>(), std::true_type());
     return hipErrorInvalidValue;   // sixteen waves are the second shape
 }
 

@@ -101,15 +101,14 @@ hipError_t launch_order(const int64_t *, int32_t n, int32_t *, hipStream_t) {
     note("{\"launch\": \"order\", \"events\": %d}", n);
     return hipSuccess;
 }
-hipError_t launch_order_pick(const FindArgs &a, int32_t *, Pick *, int64_t hits, bool defer, hipStream_t) {
-    note("{\"launch\": \"order_pick\", \"events\": %d, \"hits\": %lld, \"defer\": %d}", a.n_events, (long long)hits,
-         defer);
+hipError_t launch_order_pick(const FindArgs &a, int32_t *, Pick *, int64_t hits, hipStream_t) {
+    note("{\"launch\": \"order_pick\", \"events\": %d, \"hits\": %lld}", a.n_events, (long long)hits);
     return hipSuccess;
 }
-hipError_t launch_picked(const FindArgs &a, int threads, int lds, hipStream_t) {
-    note("{\"launch\": \"picked\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"hs_cap\": %d, \"events\": %d, \"slots\": %d}", threads,
-         lds, a.tile_rows, a.hs_cap, a.n_events, a.pool_slots);
-    return threads == 512 || threads == 256 ? hipSuccess : 1;
+hipError_t launch_picked(const FindArgs &a, int threads, int lds, bool defer, hipStream_t) {
+    note("{\"launch\": \"picked\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"hs_cap\": %d, \"events\": %d, \"slots\": %d, \"defer\": %d}",
+         threads, lds, a.tile_rows, a.hs_cap, a.n_events, a.pool_slots, defer);
+    return threads == 512 || (threads == 256 && defer) ? hipSuccess : 1;
 }
 hipError_t launch_list(const FindArgs &a, Pick *, int groups, int threads, int lds, hipStream_t) {
     note("{\"launch\": \"list\", \"threads\": %d, \"lds\": %d, \"rows\": %d, \"groups\": %d, \"stream_ok\": %d, \"split\": %d}", threads, lds,

@@ -69,7 +69,7 @@ def test_finder_kernels_keep_no_scratch(kernels):
     their working set in registers and LDS; where the event function is a call (the
     time-sliced finder, the list of events) it saves some 20 to 50 registers."""
     _, remarks = kernels
-    for kind, sizes in (("k_argmax", 3), ("k_picked", 4)):
+    for kind, sizes in (("k_argmax", 3), ("k_picked", 6)):
         scratch = _remark(remarks, kind, r"ScratchSize \[bytes/lane\]")
         assert len(scratch) == sizes and set(scratch.values()) == {0}, scratch
     for kind, sizes in (("k_tw_run", 6), ("k_list", 2)):

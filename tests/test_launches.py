@@ -127,7 +127,7 @@ def test_dense_shape(host, cfg, events, hits, most):
         return
     assert kinds == ["order_pick", "picked", "list", "compact"]
     order, dense, rest, compact = got
-    assert order["hits"] == most and order["defer"] == 0 and order["events"] == dense["events"] == events
+    assert order["hits"] == most and dense["defer"] == 0 and order["events"] == dense["events"] == events
     assert compact["ordered"] == 1
     # two workgroups per CU, a slot for each; the other shape is the context's own
     assert dense["threads"] == 512 and dense["lds"] <= (160 << 10) // 2 - 2048 and rest["threads"] == 1024 and rest["groups"] == 256
@@ -182,7 +182,7 @@ def test_large_events_on_long_rows(host, n_rho, threads, most, mode):
         for noalloc in (False, True):
             got = of(n, hits, noalloc=noalloc)
             assert [x["launch"] for x in got] == ["order_pick", "picked", "list"] + (["compact"] if n > 1 else [])
-            assert got[0]["hits"] == 2**63 - 1 and got[0]["defer"] == 1 and got[1]["threads"] == threads
+            assert got[0]["hits"] == 2**63 - 1 and got[1]["defer"] == 1 and got[1]["threads"] == threads
             assert got[1]["hs_cap"] // 64 * 64 >= most - 512
             assert got[2]["threads"] == 1024 and got[2]["stream_ok"] == 0 and got[2]["split"] == 0
             assert n == 1 or got[3]["ordered"] == (1 if n > 256 else 0)
