@@ -376,9 +376,22 @@ hough_status choose_shape(Ctx &c, std::string &why) {
     // event would take the tiled path (768 events of 272 hits on 2048 x 2048 bins:
     // 2328 -> 425 us). At T = 1 every voted bin is hot and nearly every event outgrows
     // the lists (1100 events of 65 hits on 33 x 4096 bins 4.4 ms tiled, 9.8 after a
-    // try); a configured split sweep (one workgroup of 512 threads an event, T = 40,
-    // 64 events of 77 hits on 360 x 4096 bins) is slower than the tiles, 0.48 / 0.78 ms
-    const bool fewer = g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2 && streams && g.min_votes >= 2;
+    // try). Where a bin of few votes is a candidate that another one's claim has to
+    // take (the argmax loop) or a wide window to outdo, that is so for as long as
+    // the rows are many and short, tiles / this (us), 64 events of 220 hits:
+    //                   argmax T = 2   T = 3         T = 4        nms w = 3 T = 2   T = 3
+    //   360 x 1153      2075 / 2105    1019 / 68     730 / 52     1296 / 1670       431 / 148
+    //   1500 x 1153     6592 / 6564    3430 / 4529   2378 / 96    8727 / 9314       2857 / 3334
+    //   360 x 4096      4537 / 187     1845 / 61     1077 / 50    3778 / 4279       1197 / 93
+    //   130 x 1200      1056 / 100     497 / 51      (argmax, T = 2, one event of 550 hits 1421 / 1539)
+    // (windows of w = 1 and 2 gain at any T >= 2: 1.3 times and more). A configured split
+    // sweep (one workgroup of 512 threads an event, T = 40, 64 events of 77 hits on
+    // 360 x 4096 bins) is slower than the tiles, 0.48 / 0.78 ms
+    const int many = g.peak_mode == 0 || g.nms_radius >= 3 ? g.min_votes : 4;   // votes that few enough bins reach: 4
+    const bool few_bins = many >= 4 || (many == 3 && g.n_theta * 2 <= g.n_rho) ||
+                          (many == 2 && g.peak_mode == 0 && g.n_theta * 10 <= g.n_rho);
+    const bool fewer = g.wg_threads == 0 && g.tile_rows == 0 && g.sweep_groups == 0 && g.peak_mode != 2 && streams &&
+                       g.min_votes >= 2 && few_bins;
     for (int t = 512; t >= 256 && fewer && !c.stream_ok; t /= 2) {
         std::string none;
         Shape f;

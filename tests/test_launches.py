@@ -156,7 +156,17 @@ def test_dense_shape_needs_its_workspace(host):
 
 
 @pytest.mark.parametrize("cfg,threads", [({}, 512), ({"min_votes": 2}, 512), ({"min_votes": 1}, 1024), ({"sweep_groups": 2}, 1024),
-                                         ({"rho_min": -350.0, "rho_max": 350.0}, 1024), ({"rho_min": -360.0, "rho_max": 360.0}, 512)])
+                                         ({"rho_min": -350.0, "rho_max": 350.0}, 1024), ({"rho_min": -360.0, "rho_max": 360.0}, 512),
+                                         ({"peak_mode": ARGMAX, "min_votes": 2, "n_theta": 205}, 1024),
+                                         ({"peak_mode": ARGMAX, "min_votes": 2, "n_theta": 204}, 512),
+                                         ({"peak_mode": ARGMAX, "min_votes": 3, "n_theta": 1025}, 1024),
+                                         ({"peak_mode": ARGMAX, "min_votes": 3, "n_theta": 1024}, 512),
+                                         ({"peak_mode": ARGMAX, "min_votes": 4, "n_theta": 1025}, 512),
+                                         ({"nms_radius": 2, "min_votes": 2, "n_theta": 1025}, 512),
+                                         ({"nms_radius": 3, "min_votes": 2, "n_theta": 256}, 1024),
+                                         ({"nms_radius": 3, "min_votes": 3, "n_theta": 1025}, 1024),
+                                         ({"nms_radius": 3, "min_votes": 3, "n_theta": 1024}, 512),
+                                         ({"nms_radius": 3, "min_votes": 4, "n_theta": 1025}, 512)])
 def test_long_rows_that_would_be_tiled_anyway(host, cfg, threads):
     """Where nearly every event would outgrow the lists or leaves the grid, long
     rows keep sixteen waves, as with a configured split sweep."""
