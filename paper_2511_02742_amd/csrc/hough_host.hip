@@ -131,6 +131,12 @@ constexpr int kDenseHits = 320;
 constexpr int kDenseVotes = 140000;       // hits times theta rows
 constexpr int kDenseCalm = 352;           // events of up to this many hits end no call much later (in it, their
 constexpr int kDenseCalmRows = 512;       // first sweep is not banded); on fewer rows than this, of up to 512 hits
+// Long rows: up to this many votes (hits times theta rows) in the whole call, an event
+// that is swept tile by tile stays where it is. The second launch and the choice are
+// 8 us of a call (one event of 110 hits on 64 x 2048 bins 13 / 21 us, 64 of 8 hits on 180 x
+// 2305 18 / 24), and starting such an event over is slower than sweeping it so few
+// times (65 of up to 32 hits on 64 x 4096 bins, T = 2: 39 / 65).
+constexpr int64_t kSecondVotes = 65536;
 constexpr int kBandCall = 64;             // calls of up to this many events may run k_band
 constexpr int kTwCfLds = 48 << 10;        // LDS the time-sliced finder takes at least in mode 2 (windows of about 2000 hits)
 constexpr int64_t kRegisterHits = 512;    // alive hits the finder holds in registers
@@ -706,8 +712,10 @@ hough_status enqueue_find(Ctx &c, Workspace &w, hipStream_t s, int32_t n_events,
     // A dense call's few tiled events stay: in the second launch they would come after
     // the others (776 events of 360 x 1000 bins, 3 % with a hit off the grid: 75 / 113)
     const bool wide = c.wide.max_resident > 0;
-    const bool pick = dense || (wide && w.pick != nullptr && !(n_events == 1 && n_total > list_hits(c)));
-    const Shape &f = dense ? c.dense : (wide && !pick ? c.wide : c);
+    const bool alone = n_events == 1 && n_total > list_hits(c);
+    const bool few = !alone && n_total * c.cfg.n_theta <= kSecondVotes;
+    const bool pick = dense || (wide && w.pick != nullptr && !alone && !few);
+    const Shape &f = dense ? c.dense : (wide && !pick && !few ? c.wide : c);
     const Shape &other = dense ? c : c.wide;
     hough::FindArgs a = find_args(c, f, w);
     a.n_events = n_events;

@@ -202,6 +202,23 @@ def test_large_events_on_long_rows(host, n_rho, threads, most, mode):
     assert [x["threads"] for x in of(1, most + 1, wg_threads=256) + of(2, most + 1, wg_threads=512)[:1]] == [256, 512]
 
 
+@pytest.mark.parametrize("events", [1, 2, 64, 300])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_few_votes_on_long_rows(host, events, noalloc):
+    """A call of few votes in all has no second launch: that would cost it more than
+    an event of it that is swept tile by tile; an event alone that outgrows the list
+    still has the sixteen waves."""
+    def of(hits, n_theta):
+        return [(x["launch"], x["threads"]) for x in host.calls(events, hits, n_rho=2048, n_theta=n_theta, noalloc=noalloc)
+                if x["launch"] in ("find", "picked", "list")]
+    for n_theta in (32, 64):
+        hits = 65536 // n_theta
+        assert of(hits, n_theta) == [("find", 512)]
+        assert of(hits + 1, n_theta) == [("picked", 512), ("list", 1024)]
+    hits = 65536 // 14
+    assert of(hits, 14) == [("find", 1024 if events == 1 else 512)]
+
+
 @pytest.mark.parametrize("n_rho", [1024, 1160, 2048, 4096])
 @pytest.mark.parametrize("events", [1, 2, 8, 9])
 def test_scratch_limit_of_the_call_without_allocation(host, n_rho, events):
