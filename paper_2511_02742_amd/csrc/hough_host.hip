@@ -119,8 +119,8 @@ constexpr int kSmallCall = 8;
 // tile (one of 300 among them: 580 / 20871). So such a call enqueues both
 // shapes, and k_order_pick, which reads every event's size anyway, picks one: this
 // one if no event has more hits than dense_hits() says. The other launch's
-// workgroups end at once, 3 us of a call (4096 Poisson(20) events 455 -> 458, 1024
-// argmax events of 50 tracks 134 -> 137).
+// workgroups end at once, 4 us of a call (4096 Poisson(20) events 454 -> 458, 1024
+// argmax events of 50 tracks 127 -> 131).
 constexpr int kDenseThreads = 512;
 constexpr int kDenseRho = 1000;
 constexpr int kDenseRows = 1024;
